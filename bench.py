@@ -106,8 +106,8 @@ def measure_ceilings():
 
 def apply_path(words, count):
     """Which path delta_apply_multi_sorted takes for `count` entries over
-    `words` words: the tile merge from one word in 32, the scatter below."""
-    return "tile merge" if count > 0 and count >= words // 32 else "scatter"
+    `words` words: the tile merge from one word in 18, the scatter below."""
+    return "tile merge" if count > 0 and count >= words // 18 else "scatter"
 
 
 def apply_roofline(N, K, app_s, apply_bytes, apply_achieved, apply_traffic, lines, ceiling,
@@ -126,7 +126,7 @@ def apply_roofline(N, K, app_s, apply_bytes, apply_achieved, apply_traffic, line
             "frac": round(moved / app_s / 1e9 / HBM_PEAK_GBPS, 4),
             "traffic": None,
             "algorithmic_bytes": moved,
-            "note": "a delta of at least one word in 32 touches nearly every 64-byte line; "
+            "note": "a delta of at least one word in 18 touches nearly every 64-byte line; "
                     "the merge reads and writes every word once instead of one partial-line "
                     "write per touched line",
         }

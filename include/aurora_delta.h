@@ -322,7 +322,7 @@ size_t delta_apply_multi_sorted_workspace_bytes(int32_t num_tensors);
  * flattened tensor list, Sec. 5.2 activation) for a delta whose indices are
  * strictly increasing, as delta_extract_multi writes them.  Same arguments;
  * workspace: delta_apply_multi_sorted_workspace_bytes(num_tensors).
- * When the delta holds at least one word in 32 of the tensor list, every
+ * When the delta holds at least one word in 18 of the tensor list, every
  * tile of 16384 words of each tensor is read once, patched in LDS with its
  * slice of the delta and written back whole (a delta that dense touches
  * nearly every 64-byte line, and a line written whole costs less than a

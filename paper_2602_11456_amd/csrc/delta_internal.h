@@ -277,7 +277,7 @@ hipError_t launch_apply_chain(const ChainArgs& a, hipStream_t stream);
 // (apply.hip): `entries` in all over `words` words; tiles and tile_first as
 // for launch_apply_merge.  chain_merge_pays says whether a chain is dense
 // enough for it (from one entry per 24 words; the single-delta merge pays
-// from one in 32, as the chain's other path costs more per entry than the
+// from one in 18, as the chain's other path costs more per entry than the
 // plain scatter but its merge more per tile).
 hipError_t launch_apply_runs(const uint64_t* bases, uint16_t* const* ptrs,
                              const uint64_t* tile_first, uint32_t T, uint64_t tiles,

@@ -74,7 +74,7 @@ def test_every_apply_path_matches_oracle(density):
     for w, r_ in zip(ws, ref):
         np.testing.assert_array_equal(host_u16(w), r_)
 
-    # delta_apply_multi_sorted: the tile merge from one word in 32 (10%
+    # delta_apply_multi_sorted: the tile merge from one word in 18 (10%
     # and 50% here), the scatter below
     ws = [to_dev(p) for p in prevs]
     ad.delta_apply_multi(ws, gi, gv, check=True, sorted_indices=True)
