@@ -738,16 +738,26 @@ static delta_status_t weight_table(uint16_t* const* weight_ptrs, const uint64_t*
   return DELTA_OK;
 }
 
+// Appends `part` to the words of one upload, at the next 256-byte boundary.
+static void add_words(std::vector<uint64_t>& words, const std::vector<uint64_t>& part) {
+  words.resize(align_up(8 * words.size()) / 8, 0);
+  words.insert(words.end(), part.begin(), part.end());
+}
+
 // Uploads the table into the start of the workspace (the layout of
-// delta_apply_multi_workspace_bytes).
+// delta_apply_multi_workspace_bytes), and `more` words at the boundary after
+// it: one launch per kWordBatch words in all, as every launch is about 2 us
+// of the GPU's time and 4 of the caller's.
 static hipError_t upload_weight_table(const std::vector<uint64_t>& bases,
                                       const std::vector<uint64_t>& ptrs, char* ws,
-                                      uint64_t*& d_bases, uint64_t*& d_ptrs, hipStream_t stream) {
+                                      uint64_t*& d_bases, uint64_t*& d_ptrs, hipStream_t stream,
+                                      const std::vector<uint64_t>& more = {}) {
   d_bases = (uint64_t*)ws;
   d_ptrs = (uint64_t*)(ws + align_up(8 * bases.size()));
-  hipError_t e = launch_upload_words(bases.data(), bases.size(), d_bases, stream);
-  if (e == hipSuccess && !ptrs.empty()) e = launch_upload_words(ptrs.data(), ptrs.size(), d_ptrs, stream);
-  return e;
+  std::vector<uint64_t> words = bases;
+  if (!ptrs.empty()) add_words(words, ptrs);
+  if (!more.empty()) add_words(words, more);
+  return launch_upload_words(words.data(), words.size(), d_bases, stream);
 }
 
 delta_status_t delta_apply_multi(uint16_t* const* weight_ptrs, const uint64_t* numels,
@@ -787,21 +797,21 @@ delta_status_t delta_apply_multi_sorted(uint16_t* const* weight_ptrs, const uint
   if (s != DELTA_OK) return s;
   if (count == 0) return ok();
   char* ws = (char*)workspace;
-  uint64_t *d_bases, *d_ptrs;
-  hipError_t e = upload_weight_table(bases, ptrs, ws, d_bases, d_ptrs, stream);
-  if (e != hipSuccess) return hip_fail(e, "table upload launch");
   const uint32_t T = (uint32_t)num_tensors;
   std::vector<uint64_t> tile_first(T + 1);
   const uint64_t tiles = merge_tiles(numels, T, tile_first.data());
-  if (tiles == 0 || !merge_pays(count, bases[T]) || tiles > 0xFFFFFFFFull) {
+  const bool merge = tiles > 0 && merge_pays(count, bases[T]) && tiles <= 0xFFFFFFFFull;
+  uint64_t *d_bases, *d_ptrs;
+  hipError_t e = upload_weight_table(bases, ptrs, ws, d_bases, d_ptrs, stream,
+                                     merge ? tile_first : std::vector<uint64_t>());
+  if (e != hipSuccess) return hip_fail(e, "table upload launch");
+  if (!merge) {
     e = launch_apply_multi(d_bases, (uint16_t* const*)d_ptrs, T, idx, val, count, d_error_flag,
                            stream);
     if (e != hipSuccess) return hip_fail(e, "apply_multi launch");
     return ok();
   }
   uint64_t* d_tile_first = (uint64_t*)(ws + delta_apply_multi_workspace_bytes(num_tensors));
-  e = launch_upload_words(tile_first.data(), tile_first.size(), d_tile_first, stream);
-  if (e != hipSuccess) return hip_fail(e, "tile table upload launch");
   e = launch_apply_merge(d_bases, (uint16_t* const*)d_ptrs, d_tile_first, T, tiles, idx, val,
                          count, d_error_flag, stream);
   if (e != hipSuccess) return hip_fail(e, "apply_merge launch");
@@ -869,7 +879,7 @@ delta_status_t delta_apply_chain(uint16_t* const* weight_ptrs, const uint64_t* n
   if (entries == 0) return ok();
   char* ws = (char*)workspace;
   uint64_t *d_bases, *d_ptrs;
-  hipError_t e = upload_weight_table(bases, ptrs, ws, d_bases, d_ptrs, stream);
+  hipError_t e = upload_weight_table(bases, ptrs, ws, d_bases, d_ptrs, stream, table);
   if (e != hipSuccess) return hip_fail(e, "table upload launch");
   if (num_deltas == 1) {
     e = launch_apply_multi(d_bases, (uint16_t* const*)d_ptrs, (uint32_t)num_tensors, idx_ptrs[0],
@@ -877,8 +887,6 @@ delta_status_t delta_apply_chain(uint16_t* const* weight_ptrs, const uint64_t* n
     if (e != hipSuccess) return hip_fail(e, "apply_multi launch");
     return ok();
   }
-  e = launch_upload_words(table.data(), table.size(), (uint64_t*)(ws + c.deltas), stream);
-  if (e != hipSuccess) return hip_fail(e, "delta table upload launch");
   // a chain dense enough (all its entries together at least one word in
   // 24): the tile merge of every delta, every word read and written once
   const uint32_t T = (uint32_t)num_tensors;
@@ -1034,9 +1042,8 @@ delta_status_t delta_apply_leb128_multi(uint16_t* const* weight_ptrs, const uint
   if (st != DELTA_OK) return st;
   if (nbytes == 0) return ok();   // nothing to apply
   char* ws = (char*)workspace;
-  hipError_t e = launch_upload_words(bases.data(), bases.size(), (uint64_t*)(ws + L.bases), stream);
-  if (e == hipSuccess && num_tensors > 0)
-    e = launch_upload_words(ptrs.data(), ptrs.size(), (uint64_t*)(ws + L.ptrs), stream);
+  uint64_t *d_bases, *d_ptrs;   // at L.bases and L.ptrs
+  hipError_t e = upload_weight_table(bases, ptrs, ws + L.bases, d_bases, d_ptrs, stream);
   if (e != hipSuccess) return hip_fail(e, "table upload launch");
   DecArgs a;
   memset(&a, 0, sizeof(a));
@@ -1044,13 +1051,12 @@ delta_status_t delta_apply_leb128_multi(uint16_t* const* weight_ptrs, const uint
   a.nbytes = nbytes;
   // with d_seg_bases NULL, segment t is based at tensor t's first global
   // index: the first T entries of the uploaded tensor bases
-  a.segs = {d_seg_offsets, tensor_bases ? (const uint64_t*)(ws + L.bases) : d_seg_bases, num_segs,
-            0};
+  a.segs = {d_seg_offsets, tensor_bases ? d_bases : d_seg_bases, num_segs, 0};
   a.capacity = count;
   a.d_count = (uint64_t*)(ws + L.count);
   a.err = d_error_flag;
-  a.ptrs = (uint16_t* const*)(ws + L.ptrs);
-  a.tbases = (const uint64_t*)(ws + L.bases);
+  a.ptrs = (uint16_t* const*)d_ptrs;
+  a.tbases = d_bases;
   a.num_tensors = (uint32_t)num_tensors;
   a.val = val;
   e = launch_leb128_decode(a, D, ws + L.dec, stream, true);
@@ -1202,9 +1208,9 @@ delta_status_t read_back(void* host, const void* dev, size_t n, hipStream_t stre
 
 // Workspace of delta_artifact_pack: numels [T], tensor bases [T], first
 // index byte of each tensor [T + 1], the code length, the encoder's error
-// flag, then the encoder's own workspace.
+// flag, two entry offsets, then the encoder's own workspace.
 struct PackLayout {
-  size_t numels, bases, byte_offs, nbytes, err, enc, total;
+  size_t numels, bases, byte_offs, nbytes, err, ends, enc, total;
 };
 PackLayout pack_layout(uint64_t count, int32_t T, bool leb) {
   const uint64_t t = T > 0 ? (uint64_t)T : 0;
@@ -1213,8 +1219,9 @@ PackLayout pack_layout(uint64_t count, int32_t T, bool leb) {
   L.bases = align_up(L.numels + 8 * t);
   L.byte_offs = align_up(L.bases + 8 * t);
   L.nbytes = align_up(L.byte_offs + 8 * (t + 1));
-  L.err = align_up(L.nbytes + 8);
-  L.enc = align_up(L.err + 8);
+  L.err = L.nbytes + 8;   // read back together
+  L.ends = L.err + 8;     // the first and the last entry offset
+  L.enc = align_up(L.ends + 16);
   L.total = align_up(L.enc + (leb ? enc_layout(count).total : 0));
   return L;
 }
@@ -1288,8 +1295,10 @@ delta_status_t delta_artifact_pack(const int64_t* idx, const uint16_t* val, uint
   // the entry offsets must describe `count` entries
   if (T > 0) {
     uint64_t ends[2];
-    st = read_back(&ends[0], d_tensor_offsets, 8, stream);
-    if (st == DELTA_OK) st = read_back(&ends[1], d_tensor_offsets + T, 8, stream);
+    const hipError_t er =
+        launch_pick_words(d_tensor_offsets, d_tensor_offsets + T, (uint64_t*)(ws + P.ends), stream);
+    if (er != hipSuccess) return hip_fail(er, "offsets launch");
+    st = read_back(ends, ws + P.ends, 16, stream);
     if (st != DELTA_OK) return st;
     if (ends[0] != 0 || ends[1] != count)
       return fail(DELTA_ERR_INVALID_ARG, "tensor_offsets run from %llu to %llu, not 0 to %llu",
@@ -1300,8 +1309,9 @@ delta_status_t delta_artifact_pack(const int64_t* idx, const uint16_t* val, uint
   }
   hipError_t e = hipSuccess;
   if (T > 0) {
-    e = launch_upload_words(nums.data(), T, (uint64_t*)(ws + P.numels), stream);
-    if (e == hipSuccess) e = launch_upload_words(bases.data(), T, (uint64_t*)(ws + P.bases), stream);
+    std::vector<uint64_t> words = nums;   // at P.numels, then P.bases
+    add_words(words, bases);
+    e = launch_upload_words(words.data(), words.size(), (uint64_t*)(ws + P.numels), stream);
     if (e != hipSuccess) return hip_fail(e, "table upload launch");
   }
   // The index stream starts right after the table whatever its length; with
@@ -1326,8 +1336,7 @@ delta_status_t delta_artifact_pack(const int64_t* idx, const uint16_t* val, uint
     if (e == hipSuccess) e = launch_leb128_encode(a, ws + P.enc, EL, stream);
     if (e != hipSuccess) return hip_fail(e, "encode launch");
     uint64_t got[2];
-    st = read_back(&got[0], ws + P.nbytes, 8, stream);
-    if (st == DELTA_OK) st = read_back(&got[1], ws + P.err, 8, stream);
+    st = read_back(got, ws + P.nbytes, 16, stream);
     if (st != DELTA_OK) return st;
     if (got[1] & 0xFFFFFFFFull)
       return fail(DELTA_ERR_INVALID_ARG, "indices not strictly increasing within a tensor");

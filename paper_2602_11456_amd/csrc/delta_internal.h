@@ -140,7 +140,7 @@ inline uint32_t stage_cap_for(size_t have, uint64_t tiles, uint64_t tensors, boo
 // Small host tables (tensor descriptors, bases, pointers) reach device
 // memory as kernel arguments, in batches of 64-bit words, so no host buffer
 // has to outlive the call and nothing is copied through a DMA engine.
-constexpr int kWordBatch = 320;
+constexpr int kWordBatch = 500;   // 4016 bytes of arguments with the count and the address
 struct WordBatch {
   uint64_t count;
   uint64_t w[kWordBatch];
@@ -193,6 +193,8 @@ hipError_t launch_reset(uint64_t* d_count, uint64_t* d_offsets, uint32_t num_off
                         hipStream_t stream);
 hipError_t launch_upload_words(const uint64_t* host_words, size_t nwords, uint64_t* dst,
                                hipStream_t stream);
+hipError_t launch_pick_words(const uint64_t* a, const uint64_t* b, uint64_t* dst,
+                             hipStream_t stream);
 hipError_t launch_build_tile_map(const TensorDesc* table, uint32_t num_tensors,
                                  uint32_t* tile_map, hipStream_t stream);
 // Exclusive scan of per-tile counts in groups of kTilesPerGroup tiles:

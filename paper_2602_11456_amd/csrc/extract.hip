@@ -1247,6 +1247,12 @@ __global__ void upload_words_kernel(WordBatch b, uint64_t* dst) {
   for (uint32_t i = threadIdx.x; i < b.count; i += blockDim.x) dst[i] = b.w[i];
 }
 
+// Two words that lie apart in device memory, side by side (one copy to the
+// host instead of two).
+__global__ void pick_words_kernel(const uint64_t* a, const uint64_t* b, uint64_t* dst) {
+  if (threadIdx.x < 2) dst[threadIdx.x] = threadIdx.x ? *b : *a;
+}
+
 // Row t of the table fills its tiles' map entries; a row's tiles are spread
 // over gridDim.y workgroups (the largest tensors span tens of thousands).
 __global__ void build_tile_map_kernel(const TensorDesc* table, uint32_t* tile_map) {
@@ -1279,6 +1285,12 @@ hipError_t launch_upload_words(const uint64_t* host_words, size_t nwords, uint64
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t launch_pick_words(const uint64_t* a, const uint64_t* b, uint64_t* dst,
+                             hipStream_t stream) {
+  hipLaunchKernelGGL(pick_words_kernel, dim3(1), dim3(64), 0, stream, a, b, dst);
+  return hipGetLastError();
 }
 
 hipError_t launch_build_tile_map(const TensorDesc* table, uint32_t num_tensors,

@@ -35,27 +35,11 @@ __device__ __forceinline__ uint64_t ld_le64(const uint8_t* p) {
   return v;
 }
 
-// XXH64 of [p, p + len) by the quad of lanes that this lane belongs to (q =
-// its position in the quad; all four lanes call it with the same p, len,
-// seed).  p + 8 must be 8-aligned... p itself 8-aligned.  The result is
-// valid in every lane of the quad.
-__device__ __forceinline__ uint64_t xxh64_quad(const uint8_t* p, uint64_t len, uint64_t seed,
-                                               uint32_t q, bool active) {
-  const uint64_t stripes = active ? len / 32 : 0;
-  uint64_t acc = q == 0 ? seed + kP1 + kP2 : q == 1 ? seed + kP2 : q == 2 ? seed : seed - kP1;
-  const uint64_t* w = (const uint64_t*)p + q;
-  uint64_t s = 0;
-  for (; s + 4 <= stripes; s += 4) {
-    const uint64_t x0 = w[4 * s], x1 = w[4 * s + 4], x2 = w[4 * s + 8], x3 = w[4 * s + 12];
-    acc = xx_round(acc, x0);
-    acc = xx_round(acc, x1);
-    acc = xx_round(acc, x2);
-    acc = xx_round(acc, x3);
-  }
-  for (; s < stripes; ++s) acc = xx_round(acc, w[4 * s]);
-  const uint32_t base = (threadIdx.x & 63) & ~3u;
-  const uint64_t a1 = __shfl(acc, base), a2 = __shfl(acc, base + 1), a3 = __shfl(acc, base + 2),
-                 a4 = __shfl(acc, base + 3);
+// Merges the four accumulators of the stripes (len >= 32), folds the tail
+// (fewer than 32 bytes, at t) and avalanches.
+__device__ __forceinline__ uint64_t xxh64_finish(uint64_t a1, uint64_t a2, uint64_t a3, uint64_t a4,
+                                                 uint64_t len, uint64_t seed, const uint8_t* t,
+                                                 uint64_t left) {
   uint64_t h;
   if (len >= 32) {
     h = rotl(a1, 1) + rotl(a2, 7) + rotl(a3, 12) + rotl(a4, 18);
@@ -67,29 +51,25 @@ __device__ __forceinline__ uint64_t xxh64_quad(const uint8_t* p, uint64_t len, u
     h = seed + kP5;
   }
   h += len;
-  if (active) {   // the tail, the same in every lane
-    const uint8_t* t = p + 32 * (len / 32);
-    uint64_t left = len % 32;
-    while (left >= 8) {
-      h ^= xx_round(0, ld_le64(t));
-      h = rotl(h, 27) * kP1 + kP4;
-      t += 8;
-      left -= 8;
-    }
-    if (left >= 4) {
-      const uint64_t v = (uint64_t)t[0] | ((uint64_t)t[1] << 8) | ((uint64_t)t[2] << 16) |
-                         ((uint64_t)t[3] << 24);
-      h ^= v * kP1;
-      h = rotl(h, 23) * kP2 + kP3;
-      t += 4;
-      left -= 4;
-    }
-    while (left >= 1) {
-      h ^= (uint64_t)(*t) * kP5;
-      h = rotl(h, 11) * kP1;
-      ++t;
-      --left;
-    }
+  while (left >= 8) {
+    h ^= xx_round(0, ld_le64(t));
+    h = rotl(h, 27) * kP1 + kP4;
+    t += 8;
+    left -= 8;
+  }
+  if (left >= 4) {
+    const uint64_t v = (uint64_t)t[0] | ((uint64_t)t[1] << 8) | ((uint64_t)t[2] << 16) |
+                       ((uint64_t)t[3] << 24);
+    h ^= v * kP1;
+    h = rotl(h, 23) * kP2 + kP3;
+    t += 4;
+    left -= 4;
+  }
+  while (left >= 1) {
+    h ^= (uint64_t)(*t) * kP5;
+    h = rotl(h, 11) * kP1;
+    ++t;
+    --left;
   }
   h ^= h >> 33;
   h *= kP2;
@@ -97,6 +77,51 @@ __device__ __forceinline__ uint64_t xxh64_quad(const uint8_t* p, uint64_t len, u
   h *= kP3;
   h ^= h >> 32;
   return h;
+}
+
+__device__ __forceinline__ uint64_t xxh64_start(uint32_t q, uint64_t seed) {
+  return q == 0 ? seed + kP1 + kP2 : q == 1 ? seed + kP2 : q == 2 ? seed : seed - kP1;
+}
+
+// XXH64 of [p, p + len) by the quad of lanes that this lane belongs to (q =
+// its position in the quad; all four lanes call it with the same p, len,
+// seed; p 8-aligned).  The result is valid in every lane of the quad.
+// A quad's stripes are a serial chain, and the segments of one artifact give
+// about one wavefront per two SIMDs (132 MB in 16 KiB segments: 8.1 K quads),
+// so nothing but the quad's own loads hides their latency: the kAhead
+// stripes after the ones being folded are in flight.  Cold, 16 KiB segments:
+// 132 / 4 MiB 56 / 30 us, with four loads waited for at a time 112 / 78 (819
+// MiB, where the segments fill the GPU, 240 us either way); 819 MiB in 1 MiB
+// segments 1.65 ms against 4.85.
+constexpr int kAhead = 16;
+__device__ __forceinline__ uint64_t xxh64_quad(const uint8_t* p, uint64_t len, uint64_t seed,
+                                               uint32_t q, bool active) {
+  const uint64_t stripes = active ? len / 32 : 0;
+  uint64_t acc = xxh64_start(q, seed);
+  const uint64_t* w = (const uint64_t*)p + q;
+  uint64_t s = 0;
+  if (stripes >= kAhead) {
+    uint64_t x[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) x[j] = w[4 * j];
+    for (; s + 2 * kAhead <= stripes; s += kAhead) {
+      uint64_t y[kAhead];
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) y[j] = w[4 * (s + kAhead + j)];
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) acc = xx_round(acc, x[j]);
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) x[j] = y[j];
+    }
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) acc = xx_round(acc, x[j]);
+    s += kAhead;
+  }
+  for (; s < stripes; ++s) acc = xx_round(acc, w[4 * s]);
+  const uint32_t base = (threadIdx.x & 63) & ~3u;
+  const uint64_t a1 = __shfl(acc, base), a2 = __shfl(acc, base + 1), a3 = __shfl(acc, base + 2),
+                 a4 = __shfl(acc, base + 3);
+  return xxh64_finish(a1, a2, a3, a4, len, seed, p + 32 * (len / 32), active ? len % 32 : 0);
 }
 
 // out[s] = XXH64 of segment s (seg_bytes each, the last one shorter).
@@ -114,13 +139,49 @@ __global__ __launch_bounds__(256) void xxh64_segments_kernel(const uint8_t* data
 }
 
 // Artifact hash: XXH64(table, seed = XXH64(header[0, 80), 0)); written into
-// the header (seal) or compared with it (verify).  One quad.
-__global__ void artifact_hash_kernel(uint8_t* art, uint64_t hashes_off, uint64_t nsegs,
-                                     bool seal, uint32_t* d_header_bad) {
-  const uint32_t q = threadIdx.x & 3;
-  const uint64_t h0 = xxh64_quad(art, kArtifactHashedHeader, 0, q, true);
-  const uint64_t h = xxh64_quad(art + hashes_off, 8 * nsegs, h0, q, true);
+// the header (seal) or compared with it (verify).  One workgroup of four
+// wavefronts: the table is one serial chain per accumulator (65 KB for the
+// 8.1 K segments of a 132 MB artifact: 2 K stripes), so its length is the
+// latency of one round.  Wavefront q keeps accumulator q in scalar registers
+// (a 64-bit product is four scalar multiplies there, a quarter of the vector
+// ones' latency); its lanes load word q of 64 stripes, multiply them by the
+// prime that does not depend on the accumulator, and hand them over one lane
+// at a time, two blocks of 64 stripes ahead of the chain.  2 K stripes 67 us;
+// by one quad of vector lanes, four loads waited for at a time, 160 us.
+__device__ __forceinline__ uint64_t lane_value(uint64_t x, int lane) {
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(x >> 32), lane);
+  return ((uint64_t)hi << 32) | lo;
+}
+__global__ __launch_bounds__(256) void artifact_hash_kernel(uint8_t* art, uint64_t hashes_off,
+                                                            uint64_t nsegs, bool seal,
+                                                            uint32_t* d_header_bad) {
+  __shared__ uint64_t s_acc[4];
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t stripes = nsegs / 4;   // 32 bytes of the table each
+  const uint64_t* w = (const uint64_t*)(art + hashes_off) + q;
+  const auto load = [&](uint64_t s) {
+    return s + lane < stripes ? w[4 * (s + lane)] * kP2 : 0ull;
+  };
+  uint64_t x0 = load(0), x1 = load(64);
+  const uint64_t seed0 = xxh64_quad(art, kArtifactHashedHeader, 0, lane & 3, true);
+  const uint64_t seed = lane_value(seed0, 0);
+  uint64_t acc = xxh64_start(q, seed);
+  uint64_t s = 0;
+  for (; s + 64 <= stripes; s += 64) {
+    const uint64_t x2 = load(s + 128);
+#pragma unroll
+    for (int j = 0; j < 64; ++j) acc = rotl(acc + lane_value(x0, j), 31) * kP1;
+    x0 = x1;
+    x1 = x2;
+  }
+  for (int j = 0; s + j < stripes; ++j) acc = rotl(acc + lane_value(x0, j), 31) * kP1;
+  if (lane == 0) s_acc[q] = acc;
+  __syncthreads();
   if (threadIdx.x == 0) {
+    const uint64_t h = xxh64_finish(s_acc[0], s_acc[1], s_acc[2], s_acc[3], 8 * nsegs, seed,
+                                    art + hashes_off + 32 * stripes, 8 * (nsegs % 4));
     uint64_t* field = (uint64_t*)(art + kArtifactHashField);
     if (seal)
       *field = h;
@@ -215,7 +276,7 @@ hipError_t launch_artifact_seal(uint8_t* art, const ArtifactLayout& L,
   e = launch_hash_segments(art + L.table, L.hashes - L.table, h.seg_bytes, h.version,
                            (uint64_t*)(art + L.hashes), stream);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(artifact_hash_kernel, dim3(1), dim3(64), 0, stream, art, L.hashes,
+  hipLaunchKernelGGL(artifact_hash_kernel, dim3(1), dim3(256), 0, stream, art, L.hashes,
                      L.num_segments, true, (uint32_t*)nullptr);
   return hipGetLastError();
 }
@@ -238,7 +299,7 @@ hipError_t launch_artifact_verify(const uint8_t* art, const ArtifactLayout& L, u
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(artifact_hash_kernel, dim3(1), dim3(64), 0, stream, (uint8_t*)art, L.hashes,
+  hipLaunchKernelGGL(artifact_hash_kernel, dim3(1), dim3(256), 0, stream, (uint8_t*)art, L.hashes,
                      L.num_segments, false, d_header_bad);
   return hipGetLastError();
 }

@@ -37,6 +37,35 @@ def test_hash_segments_match_oracle(n, seg):
     np.testing.assert_array_equal(got, want)
 
 
+@pytest.mark.parametrize("stripes", [1, 15, 16, 17, 31, 32, 33, 47, 48, 49])
+def test_hash_segments_around_the_stripes_in_flight(stripes):
+    """Whole segments of `stripes` 32-byte stripes, then a shorter last one
+    with a tail, on both sides of the 16 stripes a quad keeps loaded ahead."""
+    seg = 32 * stripes
+    b = rand_bytes(5 * seg + max(seg - 13, 1), seed=stripes)
+    got = ad.delta_hash_segments(torch.from_numpy(b).to(DEV), seg, seed=3)
+    np.testing.assert_array_equal(got.cpu().numpy().view(np.uint64),
+                                  oracle.hash_segments(b, seg, seed=3))
+
+
+@pytest.mark.parametrize("segments", [1, 3, 4, 255, 256, 257, 511, 512, 515, 768, 1030])
+def test_artifact_hash_by_segment_count(segments):
+    """The artifact hash where the segment hash table ends around the blocks
+    of 64 stripes (256 hashes) and around a whole stripe (4 hashes)."""
+    count = (32 * segments - 24) // 10
+    while ad.delta_artifact_layout(1, count, 8 * count, 32)["num_segments"] > segments:
+        count -= 1
+    idx = torch.arange(count, dtype=torch.int64, device=DEV)
+    val = torch.randint(-100, 100, (count,), dtype=torch.int16, device=DEV)
+    art, h = ad.pack_artifact(idx, val, torch.tensor([0, count], device=DEV), [count + 1], 8, 7,
+                              seg_bytes=32)
+    assert h.num_segments == segments
+    L = ad.delta_artifact_layout(1, count, h.idx_bytes, 32)
+    segs, want = oracle_artifact_hash(art.cpu().numpy(), L, 8, segments)
+    assert h.hash == want
+    assert ad.delta_artifact_verify(art) == (0, None, False)
+
+
 def make_versions(seed=2, density=0.02):
     g = torch.Generator().manual_seed(seed)
     shapes = [(640, 320), (17,), (1024, 300), (3, 3), (4096,)]
