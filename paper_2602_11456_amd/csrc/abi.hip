@@ -1058,6 +1058,7 @@ delta_status_t delta_apply_leb128_multi(uint16_t* const* weight_ptrs, const uint
   a.ptrs = (uint16_t* const*)d_ptrs;
   a.tbases = d_bases;
   a.num_tensors = (uint32_t)num_tensors;
+  a.words = bases[num_tensors];
   a.val = val;
   e = launch_leb128_decode(a, D, ws + L.dec, stream, true);
   if (e != hipSuccess) return hip_fail(e, "leb128 apply launch");

@@ -8,6 +8,7 @@
 // and no atomics are needed.
 #include "chain.h"
 #include "delta_internal.h"
+#include "scatter.h"
 
 namespace aurora {
 
@@ -15,28 +16,6 @@ constexpr int kApplyThreads = 256;
 
 __device__ __forceinline__ void flag_error(uint32_t* err) {
   if (err) __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// A value every lane of the wavefront holds alike, in scalar registers.
-__device__ __forceinline__ uint64_t run_uniform(uint64_t x) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
-  return ((uint64_t)hi << 32) | lo;
-}
-
-// A scattered word: streamed past the caches and, kThrough, written through
-// to memory at once ("nt sc1": non-temporal, system scope), so that the words
-// reach the memory in the order in which they leave.  A 1 / 2% delta over
-// 4.02 G words takes 1260 / 1951 us with it, 1290 / 1990 without.
-// The tensor addresses of the multi-tensor kernels come from a table in
-// memory, so the store names the global segment itself (a flat store would
-// also count against the LDS wait counter).
-template <bool kThrough>
-__device__ __forceinline__ void store_word(uint16_t* p, uint16_t v) {
-  if (kThrough)
-    asm volatile("global_store_short %0, %1, off sc1 nt" ::"v"(p), "v"((uint32_t)v) : "memory");
-  else
-    __builtin_nontemporal_store(v, (__attribute__((address_space(1))) uint16_t*)p);
 }
 
 // The scatter.  A written word costs a partial write of its 64-byte line,
@@ -64,12 +43,6 @@ __device__ __forceinline__ void store_word(uint16_t* p, uint16_t v) {
 constexpr size_t kApplyLds = 54 * 1024;
 constexpr uint32_t kApplyScatter = 256;   // threads per workgroup of the scatter
 constexpr int kApplyPer = 2;              // entries per lane
-
-// Block b of n in the order in which XCD x takes the x-th eighth.
-__device__ __forceinline__ uint64_t xcd_block(uint64_t b, uint64_t n) {
-  const uint64_t x = b % 8, q = b / 8, per = n / 8, rem = n % 8;
-  return x * per + (x < rem ? x : rem) + q;
-}
 
 // This lane's first entry; its others follow 64 apart.
 __device__ __forceinline__ uint64_t scatter_first() {
@@ -103,29 +76,13 @@ __global__ __launch_bounds__(kApplyScatter) void apply_kernel(uint16_t* __restri
   if (bad) flag_error(err);
 }
 
-// Global index -> (tensor, local index) over T tensors with bases[0..T]
-// (bases[t] = first global index of tensor t, bases[T] = total).
-__device__ __forceinline__ uint32_t find_tensor(const uint64_t* bases, uint32_t T, uint64_t g) {
-  uint32_t lo = 0, hi = T;   // answer in [lo, hi): bases[lo] <= g < bases[hi]
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (bases[mid] <= g) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
-// The tensor of the wavefront's first entry is found by the whole wavefront:
-// up to 64 R tensors, every lane holds R bases, loaded beside the entries,
-// and the bases at or below the entry are counted (R = 0: a search).  A
-// search of dependent loads in every wavefront costs more than these few
-// entries have to hide it: 2.92 against 2.52 ms (8.19 G words, 1%, 399
-// tensors).  Lanes whose entry lies in another tensor search by themselves.
+// Lanes whose entry does not lie in the tensor of the wavefront's first entry
+// search by themselves.
 template <int R>
 __global__ __launch_bounds__(kApplyScatter) void apply_multi_kernel(
     const uint64_t* __restrict__ bases, uint16_t* const* __restrict__ ptrs, uint32_t T,
     const int64_t* __restrict__ idx, const uint16_t* __restrict__ val, uint64_t count,
     uint32_t* err) {
-  const uint32_t lane = threadIdx.x & 63;
   const uint64_t k0 = scatter_first();
   int64_t g[kApplyPer];
   uint16_t v[kApplyPer];
@@ -135,24 +92,9 @@ __global__ __launch_bounds__(kApplyScatter) void apply_multi_kernel(
     g[u] = k < count ? idx[k] : -1;
     v[u] = k < count ? val[k] : 0;
   }
-  uint64_t b[R > 0 ? R : 1];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const uint32_t p = 64 * r + lane;
-    b[r] = p < T ? bases[p] : ~0ull;
-  }
   const uint64_t total = bases[T];
-  const uint64_t first = run_uniform(g[0] < 0 ? 0 : (uint64_t)g[0]);
-  uint32_t t = 0;
-  if (R > 0) {
-    uint32_t c = 0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) c += (uint32_t)__builtin_popcountll(__ballot(b[r] <= first));
-    t = c ? c - 1 : 0;
-  } else {
-    t = find_tensor(bases, T, first);
-  }
-  t = __builtin_amdgcn_readfirstlane(t);
+  const WaveBases<R> b(bases, T);
+  const uint32_t t = b.tensor(bases, T, run_uniform(g[0] < 0 ? 0 : (uint64_t)g[0]));
   const uint64_t lo = bases[t], hi = bases[T ? t + 1 : t];
   uint16_t* const w = T ? ptrs[t] : nullptr;
   bool bad = false;

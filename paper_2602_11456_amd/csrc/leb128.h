@@ -39,12 +39,14 @@ struct EncArgs {
   EncTileSegs* tile_segs;       // per tile (with segments)
 };
 
-// A 16 KiB decode tile's first entry and, with segments, the first and the
-// last segment of its entries and the first entry of the first.
+// A 4 KiB decode tile's first entry and, with segments, the first and the
+// last segment of its entries and the first entry of the first; generic: an
+// entry of it may open a segment, or a number of it takes over two bytes.
 struct DecTileRec {
   uint64_t e0;
   uint32_t first, last;
   uint64_t lo0;
+  uint32_t generic;
 };
 
 struct DecArgs {
@@ -61,12 +63,14 @@ struct DecArgs {
   uint64_t* tile_v;             // segmented sum of the tile's terms
   uint32_t* wave_f;             // the same per wavefront of a tile (4 per tile)
   uint64_t* wave_v;
+  uint16_t* wave_t;             // numbers ending in each wavefront's bytes
   // Decode-in-apply (launch_leb128_decode with apply set): instead of
   // writing index k, write val[k] to the word of the tensor list that
   // decoded index names.
   uint16_t* const* ptrs;        // device [num_tensors]
   const uint64_t* tbases;       // device [num_tensors + 1]: first index of each tensor, total
   uint32_t num_tensors;
+  uint64_t words;               // of all tensors
   const uint16_t* val;          // device [capacity]
   uint64_t* gexcl_v;            // index just before each group of tiles
   DecTileRec* tile_recs;        // per byte tile (dec_recs_kernel)
@@ -80,7 +84,7 @@ struct EncLayout {
 uint32_t enc_grid(uint64_t count, bool count_on_device);
 struct DecLayout {
   uint64_t btiles;
-  size_t tile_terms, group_sum, group_excl, tile_f, tile_v, wave_f, wave_v, gsum_f, gsum_v,
+  size_t tile_terms, group_sum, group_excl, tile_f, tile_v, wave_f, wave_v, wave_t, gsum_f, gsum_v,
       gexcl_v, tile_recs, total;
 };
 EncLayout enc_layout(uint64_t count);

@@ -16,16 +16,20 @@
 // scanned in groups (the same group scan as extract), and enc_copy moves
 // every tile's code to its place.
 //
-// Decode, per tile of 16 KiB of bytes: dec_count counts the terminating
-// bytes (high bit clear; 4 bytes per 32-bit test); their scan numbers the
-// entries.  dec_fold decodes every number (a terminating byte and the
-// continuation bytes before it, at most 10) and folds the tile into a
-// segmented sum: an entry that opens a segment contributes base + term and
-// restarts the sum, any other adds its gap.  Those tile folds are scanned
-// (segmented), and dec_write decodes again and writes every index as the
-// segmented running sum.
+// Decode, per tile of 4 KiB of bytes (a wavefront takes 1 KiB, 16 bytes per
+// lane): dec_sum counts the numbers that end in the tile (bytes with the high
+// bit clear) and sums them, four bytes per instruction, as long as none takes
+// over two bytes; the scan of the counts numbers the entries.  Only a tile in
+// which a segment may open, or which holds a longer number (a generic tile),
+// is decoded number by number by dec_fold (a terminating byte and the
+// continuation bytes before it, at most 10) and folded into a segmented sum:
+// an entry that opens a segment contributes base + term and restarts the sum,
+// any other adds its gap.  The tile sums are scanned (segmented), and
+// dec_write decodes again and writes every index as the segmented running
+// sum.
 #include "delta_internal.h"
 #include "leb128.h"
+#include "scatter.h"
 
 namespace aurora {
 
@@ -34,8 +38,8 @@ constexpr int kLebWaves = kLebThreads / 64;
 constexpr int kEncSteps = 16;                    // 64-entry steps per wavefront
 constexpr int kEncWave = 64 * kEncSteps;         // 1024 entries
 constexpr int kEncTile = kLebWaves * kEncWave;   // 4096 entries
-constexpr int kDecWave = 4096;                   // bytes per wavefront
-constexpr int kDecTile = kLebWaves * kDecWave;   // 16 KiB
+constexpr int kDecWave = 1024;                   // bytes per wavefront, 16 per lane
+constexpr int kDecTile = kLebWaves * kDecWave;   // 4 KiB
 constexpr int kDecBack = 16;                     // bytes kept before a tile (>= 9)
 constexpr int kSegLds = 256;                     // segment starts cached per tile
 
@@ -455,14 +459,6 @@ __global__ void enc_seg_fix_kernel(EncArgs a) {
 
 // ---------------------------------------------------------------- decode
 
-// Terminating bytes (high bit clear) among the 4 bytes of w whose
-// positions p0 .. p0+3 are below n.
-__device__ __forceinline__ uint32_t terms_in_word(uint32_t w, uint64_t p0, uint64_t n) {
-  uint32_t m = ~w & 0x80808080u;
-  if (p0 + 4 > n) m &= p0 >= n ? 0u : (0xFFFFFFFFu >> (8 * (4 - (n - p0))));
-  return __builtin_popcount(m);
-}
-
 typedef uint32_t leb_u32x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(1))) leb_u32x4* leb_gvec_ptr;
 
@@ -477,33 +473,95 @@ __device__ __forceinline__ uint4 load16(const uint8_t* in, uint64_t p, uint64_t 
   return {w[0], w[1], w[2], w[3]};
 }
 
-__global__ __launch_bounds__(kLebThreads) void dec_count_kernel(DecArgs a, bool aligned) {
-  __shared__ uint32_t s_wave[kLebWaves];
-  const uint64_t b0 = (uint64_t)blockIdx.x * kDecTile;
-  uint32_t c = 0;
-  if (aligned) {
-#pragma unroll
-    for (int j = 0; j < kDecTile / 16 / kLebThreads; ++j) {
-      const uint64_t p = b0 + 16ull * (j * kLebThreads + threadIdx.x);
-      if (p < a.nbytes) {
-        const uint4 v = load16(a.in, p, a.nbytes);
-        c += terms_in_word(v.x, p, a.nbytes) + terms_in_word(v.y, p + 4, a.nbytes) +
-             terms_in_word(v.z, p + 8, a.nbytes) + terms_in_word(v.w, p + 12, a.nbytes);
-      }
-    }
+// The 16 bytes of a lane, at any alignment; bytes at or past n read as 0x80
+// (they neither end a number nor add to one).  `prev` is the byte before
+// them (0 before the first of the stream); `open`, in lane 0: the two bytes
+// before them belong to one number that goes on.
+typedef uint32_t leb_u32x4u __attribute__((ext_vector_type(4), aligned(1)));
+typedef const __attribute__((address_space(1))) leb_u32x4u* leb_gvecu_ptr;
+struct LaneBytes {
+  leb_u32x4 c;
+  uint32_t prev;
+  bool open;
+};
+__device__ __forceinline__ LaneBytes lane_bytes(const uint8_t* in, uint64_t p, uint64_t n) {
+  LaneBytes b;
+  const bool look = lane_id() == 0 && p <= n;
+  const uint32_t before = (look && p > 0) ? in[p - 1] : 0u;
+  b.open = ((look && p > 1) ? in[p - 2] : 0u) & before & 0x80u;
+  if (p + 16 <= n) {
+    const leb_u32x4u v = *(leb_gvecu_ptr)(uintptr_t)(in + p);
+    b.c = leb_u32x4{v.x, v.y, v.z, v.w};
   } else {
-    for (uint32_t i = threadIdx.x; i < (uint32_t)kDecTile; i += kLebThreads) {
-      const uint64_t p = b0 + i;
-      if (p < a.nbytes && !(a.in[p] & 0x80)) ++c;
-    }
+    b.c = leb_u32x4{0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u};
+    for (uint32_t i = 0; i < 16 && p + i < n; ++i)
+      b.c[i >> 2] ^= (uint32_t)(in[p + i] ^ 0x80u) << (8 * (i & 3));
   }
-  c = wave_sum(c);
-  if (lane_id() == 0) s_wave[wave_id()] = c;
+  const uint32_t up = __shfl_up(b.c[3] >> 24, 1);
+  b.prev = lane_id() == 0 ? before : up;
+  return b;
+}
+
+// Sums over the 16 bytes of a lane, four bytes at a time: how many numbers
+// end there, and their sum, if each has one byte or two (the byte before its
+// last one continues into it).  `longer`: one has more.
+__device__ __forceinline__ void lane_sums(const LaneBytes& b, uint64_t p, uint64_t n,
+                                          uint32_t& terms, uint32_t& sum, bool& longer) {
+  terms = 0;
+  uint32_t ones = 0, twos = 0, l = 0;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const uint32_t w = b.c[d];
+    const uint32_t before = d ? b.c[d - 1] : b.prev << 24;
+    const uint32_t wp = __builtin_amdgcn_alignbyte(w, before, 3);   // each byte's predecessor
+    const uint32_t e = (~w & 0x80808080u) >> 7, c = (wp & 0x80808080u) >> 7;
+    const uint32_t em = (e << 8) - e, cm = (c << 8) - c;   // 0xFF in the bytes of the flags
+    const uint32_t pay = w & 0x7F7F7F7Fu & em;
+    terms += __builtin_popcount(e);
+    ones = __builtin_amdgcn_sad_u8(pay, 0, ones);
+    ones = __builtin_amdgcn_sad_u8(wp & 0x7F7F7F7Fu & em & cm, 0, ones);
+    twos = __builtin_amdgcn_sad_u8(pay & cm, 0, twos);
+    // two continuation bytes in a row, inside the stream
+    const uint64_t q = p + 4 * d;
+    const uint32_t valid = q + 4 <= n ? ~0u : q >= n ? 0u : 0xFFFFFFFFu >> (8 * (4 - (n - q)));
+    l |= w & wp & 0x80808080u & valid;
+  }
+  sum = ones + 127 * twos;
+  longer = l != 0 || b.open;
+}
+
+__global__ __launch_bounds__(kLebThreads) void dec_sum_kernel(DecArgs a) {
+  __shared__ uint64_t s_sum[kLebWaves];   // terms << 32 | sum: both below 2^32
+  __shared__ uint32_t s_longer[kLebWaves];
+  const uint64_t tile = blockIdx.x;
+  const uint32_t lane = lane_id(), wave = wave_id();
+  const uint64_t p = tile * kDecTile + wave * kDecWave + 16 * lane;
+  const LaneBytes b = lane_bytes(a.in, p, a.nbytes);
+  uint32_t terms, sum;
+  bool longer;
+  lane_sums(b, p, a.nbytes, terms, sum, longer);
+  // the stream must not end inside a number
+  if (a.nbytes > p && a.nbytes <= p + 16 && (a.in[a.nbytes - 1] & 0x80)) raise_flag(a.err);
+  const uint64_t s = wave_sum(((uint64_t)terms << 32) | sum);
+  const uint64_t lm = __ballot(longer);
+  if (lane == 0) {
+    s_sum[wave] = s;
+    s_longer[wave] = lm != 0;
+    a.wave_t[tile * kLebWaves + wave] = (uint16_t)(s >> 32);
+    a.wave_f[tile * kLebWaves + wave] = 0;
+    a.wave_v[tile * kLebWaves + wave] = (uint32_t)s;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    uint32_t t = 0;
-    for (int w = 0; w < kLebWaves; ++w) t += s_wave[w];
-    a.tile_terms[blockIdx.x] = t;
+    uint64_t t = 0;
+    uint32_t l = 0;
+    for (int w = 0; w < kLebWaves; ++w) {
+      t += s_sum[w];
+      l |= s_longer[w];
+    }
+    a.tile_terms[tile] = (uint32_t)(t >> 32);
+    a.tile_v[tile] = (uint32_t)t;
+    a.tile_f[tile] = l;   // until dec_recs: holds a longer number
   }
 }
 
@@ -531,30 +589,49 @@ __device__ __forceinline__ void dec_load_tile(const DecArgs& a, uint64_t b0, boo
   __syncthreads();
 }
 
-// Terminating bytes in this wavefront's 4 KiB of the tile (from LDS).
-__device__ __forceinline__ uint32_t dec_wave_terms(const uint8_t* s_bytes, uint64_t b0,
-                                                   uint64_t n) {
-  const uint32_t* w32 = (const uint32_t*)(s_bytes + kDecBack) + wave_id() * (kDecWave / 4);
-  const uint64_t pw = b0 + (uint64_t)wave_id() * kDecWave;
-  uint32_t c = 0;
-#pragma unroll 4
-  for (int j = 0; j < kDecWave / 4 / 64; ++j) {
-    const uint32_t q = j * 64 + lane_id();
-    c += terms_in_word(w32[q], pw + 4ull * q, n);
-  }
-  return wave_sum(c);
-}
-
 // First entry id of this wavefront in the tile whose first is e0.
-__device__ __forceinline__ uint64_t dec_wave_e0(uint64_t e0, const uint32_t* s_wterm) {
+__device__ __forceinline__ uint64_t dec_wave_e0(const DecArgs& a, uint64_t tile, uint64_t e0) {
   uint64_t e = e0;
-  for (uint32_t w = 0; w < wave_id(); ++w) e += s_wterm[w];
+  for (uint32_t w = 0; w < wave_id(); ++w) e += a.wave_t[tile * kLebWaves + w];
   return e;
 }
 
-// Every lane decodes 16 bytes per step: a wavefront covers 1 KiB per step
-// and 4 KiB in kDecSteps steps.
-constexpr int kDecSteps = kDecWave / (64 * 16);
+// Segmented fold of tiles [lo, end) (end - lo <= 64) by one wavefront.
+__device__ __forceinline__ void seg_fold_tiles(const uint32_t* f, const uint64_t* v, uint64_t lo,
+                                               uint64_t end, uint32_t& out_f, uint64_t& out_v) {
+  const uint64_t t = lo + lane_id();
+  const bool in = t < end;
+  const uint32_t tf = in ? f[t] : 0;
+  const uint64_t tv = in ? v[t] : 0;
+  const uint64_t fm = __ballot(tf != 0);
+  uint64_t x = tv;
+  if (fm) {
+    const uint32_t L = 63 - __builtin_clzll(fm);
+    x = lane_id() >= L ? tv : 0;
+  }
+  out_f = fm != 0;
+  out_v = wave_sum(x);
+}
+
+// Index of the entry before the tile's first, by one wavefront.
+__device__ __forceinline__ uint64_t dec_tile_carry(const DecArgs& a, uint64_t tile) {
+  const uint64_t g = tile / kTilesPerGroup;
+  uint32_t f;
+  uint64_t v;
+  seg_fold_tiles(a.tile_f, a.tile_v, g * kTilesPerGroup, tile, f, v);
+  return f ? v : a.gexcl_v[g] + v;
+}
+
+// Index of the entry before this wavefront's first, given the one before the
+// tile's, from the wavefronts' sums.
+__device__ __forceinline__ uint64_t dec_wave_carry(const DecArgs& a, uint64_t tile, uint64_t run) {
+  for (uint32_t w = 0; w < wave_id(); ++w)
+    run = a.wave_f[tile * kLebWaves + w] ? a.wave_v[tile * kLebWaves + w]
+                                         : run + a.wave_v[tile * kLebWaves + w];
+  return run;
+}
+
+static_assert(kDecWave == 64 * 16, "every lane decodes 16 bytes");
 
 // Byte j (0..15) of 16 bytes held as four dwords.
 __device__ __forceinline__ uint32_t byte16(const leb_u32x4& v, int j) {
@@ -681,9 +758,9 @@ struct LaneDec {
 };
 
 __device__ __forceinline__ void dec_lane_step(const DecArgs& a, const uint8_t* s_bytes,
-                                              uint64_t b0, int it, uint64_t& e_step,
+                                              uint64_t b0, uint64_t& e_step,
                                               LaneDec& d, bool& bad) {
-  const uint32_t q = wave_id() * kDecWave + it * 1024 + lane_id() * 16;   // tile offset
+  const uint32_t q = wave_id() * kDecWave + lane_id() * 16;   // tile offset
   const uint64_t p = b0 + q;
   const leb_u32x4 C = *(const leb_u32x4*)(s_bytes + kDecBack + q);
   const leb_u32x4 P = *(const leb_u32x4*)(s_bytes + kDecBack + q - 16);
@@ -747,24 +824,14 @@ __device__ __forceinline__ void dec_wave_fold(const DecArgs& a, const TileSegs& 
                                               const uint64_t* s_lo, const uint8_t* s_bytes,
                                               uint64_t b0, uint64_t e, bool& bad, uint32_t& f,
                                               uint64_t& v) {
-  f = 0;
-  v = 0;
-  for (int it = 0; it < kDecSteps; ++it) {
-    LaneDec d;
-    dec_lane_step(a, s_bytes, b0, it, e, d, bad);
-    uint32_t lf;
-    uint64_t lv;
-    lane_fold(a, c, s_lo, d, lf, lv);
-    wave_seg_scan(lf, lv);
-    const uint32_t sf = __shfl(lf, 63);
-    const uint64_t sv = __shfl(lv, 63);
-    if (sf) {
-      f = 1;
-      v = sv;
-    } else {
-      v += sv;
-    }
-  }
+  LaneDec d;
+  dec_lane_step(a, s_bytes, b0, e, d, bad);
+  uint32_t lf;
+  uint64_t lv;
+  lane_fold(a, c, s_lo, d, lf, lv);
+  wave_seg_scan(lf, lv);
+  f = __shfl(lf, 63);
+  v = __shfl(lv, 63);
 }
 
 // First entry and segment range of every byte tile, after the count scan:
@@ -778,12 +845,17 @@ __global__ __launch_bounds__(256) void dec_recs_kernel(DecArgs a, uint64_t btile
   const uint32_t terms = t < btiles ? a.tile_terms[t] : 0u;
   const uint32_t incl = wave_incl_scan(terms);
   if (t >= btiles) return;
-  DecTileRec r{a.group_excl[g] + (incl - terms), 0u, 0u, 0ull};
+  DecTileRec r{a.group_excl[g] + (incl - terms), 0u, 0u, 0ull, 0u};
   if (terms && a.segs.num) {
     r.first = seg_of(a.segs, r.e0);
     r.last = seg_of(a.segs, r.e0 + terms - 1);
     r.lo0 = a.segs.offs[r.first];
   }
+  // generic: a longer number, or an entry that may open a segment (entry 0,
+  // the first of a segment that starts here, or any past the first segment)
+  const bool opens = r.e0 == 0 || (a.segs.num && (r.first != r.last || r.lo0 >= r.e0));
+  r.generic = a.tile_f[t] != 0 || (terms && opens);
+  a.tile_f[t] = 0;   // a generic tile's is written by dec_fold
   a.tile_recs[t] = r;
 }
 
@@ -808,35 +880,19 @@ __device__ __forceinline__ TileSegs dec_tile_segs(const DecArgs& a, const DecTil
 __global__ __launch_bounds__(kLebThreads) void dec_fold_kernel(DecArgs a, bool aligned) {
   __shared__ __align__(16) uint8_t s_bytes[kDecBack + kDecTile];
   __shared__ uint64_t s_lo[kSegLds];
-  __shared__ uint32_t s_wterm[kLebWaves];
   __shared__ uint32_t s_wf[kLebWaves];
   __shared__ uint64_t s_wv[kLebWaves];
   const uint64_t tile = blockIdx.x;
   const uint64_t b0 = tile * kDecTile;
   const DecTileRec rec = a.tile_recs[tile];
+  if (!rec.generic) return;   // uniform: dec_sum's sums stand
   dec_load_tile(a, b0, aligned, s_bytes);                                    // barrier
-  const uint64_t e0 = rec.e0;
-  const uint32_t terms = a.tile_terms[tile];
-  const uint32_t wt = dec_wave_terms(s_bytes, b0, a.nbytes);
-  if (lane_id() == 0) s_wterm[wave_id()] = wt;
   const TileSegs c = dec_tile_segs(a, rec, s_lo);
   __syncthreads();
   bool bad = false;
-  if (terms == 0) {   // uniform: no number ends in this tile
-    if (threadIdx.x == 0) {
-      a.tile_f[tile] = 0;
-      a.tile_v[tile] = 0;
-    }
-    const uint64_t last = a.nbytes - 1;   // the stream must not end inside a number
-    if (threadIdx.x == 0 && last >= b0 && last < b0 + kDecTile &&
-        (s_bytes[kDecBack + (last - b0)] & 0x80))
-      bad = true;
-    if (bad) raise_flag(a.err);
-    return;
-  }
   uint32_t f;
   uint64_t v;
-  dec_wave_fold(a, c, s_lo, s_bytes, b0, dec_wave_e0(e0, s_wterm), bad, f, v);
+  dec_wave_fold(a, c, s_lo, s_bytes, b0, dec_wave_e0(a, tile, rec.e0), bad, f, v);
   if (lane_id() == 0) {
     s_wf[wave_id()] = f;
     s_wv[wave_id()] = v;
@@ -859,23 +915,6 @@ __global__ __launch_bounds__(kLebThreads) void dec_fold_kernel(DecArgs a, bool a
     a.tile_v[tile] = tv;
   }
   if (bad) raise_flag(a.err);
-}
-
-// Segmented fold of tiles [lo, end) (end - lo <= 64) by one wavefront.
-__device__ __forceinline__ void seg_fold_tiles(const uint32_t* f, const uint64_t* v, uint64_t lo,
-                                               uint64_t end, uint32_t& out_f, uint64_t& out_v) {
-  const uint64_t t = lo + lane_id();
-  const bool in = t < end;
-  const uint32_t tf = in ? f[t] : 0;
-  const uint64_t tv = in ? v[t] : 0;
-  const uint64_t fm = __ballot(tf != 0);
-  uint64_t x = tv;
-  if (fm) {
-    const uint32_t L = 63 - __builtin_clzll(fm);
-    x = lane_id() >= L ? tv : 0;
-  }
-  out_f = fm != 0;
-  out_v = wave_sum(x);
 }
 
 __global__ __launch_bounds__(64) void seg_group_sum_kernel(const uint32_t* tile_f,
@@ -931,234 +970,237 @@ __global__ __launch_bounds__(kSegScanThreads) void seg_group_scan_kernel(const u
   if (d_total && threadIdx.x == 0) *d_total = s_carry;
 }
 
-// Entries one wavefront decodes in one step, at most (64 lanes x 16 bytes).
-constexpr int kDecStepEntries = 64 * 16;
+// Entries one wavefront decodes, at most (64 lanes x 16 bytes).
+constexpr int kDecWaveEntries = 64 * 16;
+constexpr int kDecApplyBases = 8;   // up to 512 tensors found without a search
+
+// A wavefront's decoded entries, staged in LDS so that they leave coalesced:
+// offsets from an index (a tile that is not generic), or the indices.
+union WaveOut {
+  uint32_t off[kDecWaveEntries + 64];   // and a slot per lane that nothing reads
+  uint64_t idx[kDecWaveEntries];
+};
+
+// Publishes a wavefront's LDS writes to its own lanes (its LDS operations
+// complete in order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Not a generic tile: numbers of one or two bytes, none of which opens a
+// segment.  Stages the offset of every number's index from the index before
+// the wavefront's first; returns how many there are.  No chain over the
+// bytes: each one needs only the byte before it.
+__device__ __forceinline__ uint32_t dec_wave_short(const DecArgs& a, uint64_t tile, WaveOut& so) {
+  const uint32_t lane = lane_id();
+  const uint64_t p = tile * kDecTile + wave_id() * kDecWave + 16 * lane;
+  const LaneBytes b = lane_bytes(a.in, p, a.nbytes);
+  uint32_t terms, sum;
+  bool longer;
+  lane_sums(b, p, a.nbytes, terms, sum, longer);
+  const uint64_t both = ((uint64_t)terms << 32) | sum;
+  const uint64_t incl = wave_incl_scan(both);
+  uint32_t at = (uint32_t)((incl - both) >> 32), o = (uint32_t)(incl - both);
+  uint32_t prev = b.prev;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const uint32_t x = byte16(b.c, j);
+    const uint32_t pay = x & 0x7Fu;
+    const uint32_t num = (prev & 0x80u) ? (pay << 7) | (prev & 0x7Fu) : pay;
+    const bool end = !(x & 0x80u);
+    o += end ? num : 0u;
+    so.off[end ? at : kDecWaveEntries + lane] = o;
+    at += end ? 1u : 0u;
+    prev = x;
+  }
+  wave_lds_fence();
+  return (uint32_t)(__shfl(incl, 63) >> 32);
+}
+
+// A generic tile: every number in full, segments followed.  Stages the
+// indices of this wavefront's entries, the first of which is entry e and
+// follows index `run`; returns how many there are.
+__device__ __forceinline__ uint32_t dec_wave_generic(const DecArgs& a, const TileSegs& c,
+                                                     const uint64_t* s_lo, const uint8_t* s_bytes,
+                                                     uint64_t tile, uint64_t e, uint64_t run,
+                                                     WaveOut& so) {
+  bool bad = false;   // reported by dec_fold
+  const uint64_t e_step = e;
+  LaneDec d;
+  dec_lane_step(a, s_bytes, tile * kDecTile, e, d, bad);
+  uint32_t lf;
+  uint64_t lv;
+  lane_fold(a, c, s_lo, d, lf, lv);
+  // index before this lane's first number: segmented exclusive scan
+  uint32_t sf = lf;
+  uint64_t sv = lv;
+  wave_seg_scan(sf, sv);
+  uint32_t xf = __shfl_up(sf, 1);
+  uint64_t xv = __shfl_up(sv, 1);
+  if (lane_id() == 0) {
+    xf = 0;
+    xv = 0;
+  }
+  uint64_t y = xf ? xv : run + xv;
+  if (d.ends) {
+    SegCursor r = seg_cursor(a.segs, c, s_lo, d.e);
+    uint64_t k = d.e;
+    if (!lane_opens(a.segs, r, d)) {   // the common case: running sums
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        if ((d.ends >> j) & 1u) {
+          y += d.num[j];
+          so.idx[k - e_step] = y;
+          ++k;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        if ((d.ends >> j) & 1u) {
+          int64_t base;
+          y = seg_step(a.segs, c, s_lo, r, k, base) ? d.num[j] + (uint64_t)base : y + d.num[j];
+          so.idx[k - e_step] = y;
+          ++k;
+        }
+      }
+    }
+  }
+  wave_lds_fence();
+  return (uint32_t)(e - e_step);
+}
 
 __global__ __launch_bounds__(kLebThreads) void dec_write_kernel(DecArgs a, bool aligned) {
   __shared__ __align__(16) uint8_t s_bytes[kDecBack + kDecTile];
   __shared__ uint64_t s_lo[kSegLds];
-  __shared__ uint32_t s_wterm[kLebWaves];
-  __shared__ uint64_t s_carry;
-  // every wavefront's decoded indices of one step, written out coalesced
-  __shared__ uint64_t s_out[kLebWaves][kDecStepEntries];
+  __shared__ WaveOut s_out[kLebWaves];
   const uint64_t tile = blockIdx.x;
   const uint32_t terms = a.tile_terms[tile];
   if (terms == 0) return;   // uniform
-  const uint64_t b0 = tile * kDecTile;
   const DecTileRec rec = a.tile_recs[tile];
-  dec_load_tile(a, b0, aligned, s_bytes);                                    // barrier
-  const uint64_t e0 = rec.e0;
-  if (e0 >= a.capacity) return;   // uniform: nothing of this tile is kept
-  const uint32_t lane = lane_id(), wave = wave_id();
-  if (threadIdx.x < 64) {   // index of the entry just before the tile
-    const uint64_t g = tile / kTilesPerGroup;
-    uint32_t f;
-    uint64_t v;
-    seg_fold_tiles(a.tile_f, a.tile_v, g * kTilesPerGroup, tile, f, v);
-    if (threadIdx.x == 0) s_carry = f ? v : a.gexcl_v[g] + v;
+  if (rec.e0 >= a.capacity) return;   // uniform: nothing of this tile is kept
+  const uint32_t lane = lane_id();
+  const uint64_t run = dec_wave_carry(a, tile, dec_tile_carry(a, tile));
+  const uint64_t e = dec_wave_e0(a, tile, rec.e0);
+  WaveOut& so = s_out[wave_id()];
+  if (!rec.generic) {   // uniform
+    const uint32_t n = dec_wave_short(a, tile, so);
+    for (uint32_t i = lane; i < n; i += 64)
+      if (e + i < a.capacity) a.out[e + i] = (int64_t)(run + so.off[i]);
+    return;
   }
-  const uint32_t wt = dec_wave_terms(s_bytes, b0, a.nbytes);
-  if (lane == 0) s_wterm[wave] = wt;
+  dec_load_tile(a, tile * kDecTile, aligned, s_bytes);   // barrier
   const TileSegs c = dec_tile_segs(a, rec, s_lo);
   __syncthreads();
-  const uint64_t ew = dec_wave_e0(e0, s_wterm);
-  // index of the entry before this wavefront's first, from dec_fold's
-  // per-wavefront folds
-  uint64_t run = s_carry;
-  for (uint32_t w = 0; w < wave; ++w)
-    run = a.wave_f[tile * kLebWaves + w] ? a.wave_v[tile * kLebWaves + w]
-                                         : run + a.wave_v[tile * kLebWaves + w];
-  bool bad = false;   // reported by dec_fold
-  uint64_t* so = s_out[wave];
-  uint64_t e = ew;
-  for (int it = 0; it < kDecSteps; ++it) {
-    const uint64_t e_step = e;
-    LaneDec d;
-    dec_lane_step(a, s_bytes, b0, it, e, d, bad);
-    uint32_t lf;
-    uint64_t lv;
-    lane_fold(a, c, s_lo, d, lf, lv);
-    // index before this lane's first number: segmented exclusive scan
-    uint32_t sf = lf;
-    uint64_t sv = lv;
-    wave_seg_scan(sf, sv);
-    uint32_t xf = __shfl_up(sf, 1);
-    uint64_t xv = __shfl_up(sv, 1);
-    if (lane == 0) {
-      xf = 0;
-      xv = 0;
-    }
-    uint64_t y = xf ? xv : run + xv;
-    const uint32_t f63 = __shfl(sf, 63);
-    const uint64_t v63 = __shfl(sv, 63);
-    run = f63 ? v63 : run + v63;
-    if (d.ends) {
-      SegCursor r = seg_cursor(a.segs, c, s_lo, d.e);
-      uint64_t k = d.e;
-      if (!lane_opens(a.segs, r, d)) {   // the common case: running sums
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          if ((d.ends >> j) & 1u) {
-            y += d.num[j];
-            so[k - e_step] = y;
-            ++k;
-          }
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          if ((d.ends >> j) & 1u) {
-            int64_t base;
-            y = seg_step(a.segs, c, s_lo, r, k, base) ? d.num[j] + (uint64_t)base : y + d.num[j];
-            so[k - e_step] = y;
-            ++k;
-          }
-        }
-      }
-    }
-    // the wavefront's entries of this step are contiguous: store them
-    // coalesced from LDS (LDS operations of one wavefront complete in order)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const uint32_t n = (uint32_t)(e - e_step);
-    for (uint32_t i = lane; i < n; i += 64) {
-      const uint64_t k = e_step + i;
-      if (k < a.capacity) a.out[k] = (int64_t)so[i];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();   // so[] is rewritten by the next step
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-}
-
-// Global index -> tensor holding it (tbases[t] <= y < tbases[t + 1]).
-__device__ __forceinline__ uint32_t dec_find_tensor(const uint64_t* tbases, uint32_t T,
-                                                    uint64_t y) {
-  uint32_t lo = 0, hi = T;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (tbases[mid] <= y) lo = mid; else hi = mid;
-  }
-  return lo;
+  const uint32_t n = dec_wave_generic(a, c, s_lo, s_bytes, tile, e, run, so);
+  for (uint32_t i = lane; i < n; i += 64)
+    if (e + i < a.capacity) a.out[e + i] = (int64_t)so.idx[i];
 }
 
 // Decode-in-apply: decodes like dec_write_kernel, but every number's
 // index y receives its entry's word, w[y] = val[k] in the tensor holding
-// y, with no index stream written.  Each step's indices are staged in LDS
-// so that, as in the plain apply, every store instruction covers 64
-// consecutive entries and the words are loaded coalesced.  Entries past
-// the value count, indices outside the tensor list, and a stream whose
-// entry count differs from the value count raise the error flag; those
-// words are left alone.
+// y, with no index stream written.  The tile's indices are staged in LDS and
+// the workgroup stores them together, 256 consecutive entries at a time, so
+// that, as in the plain apply, the words written at one time lie close
+// together; all of a lane's words are loaded before its first store, because
+// a load's data is taken only once the stores before it are done.  Entries
+// past the value count, indices outside the tensor list, and a stream whose
+// entry count differs from the value count raise the error flag; those words
+// are left alone.
+//
+// As for the plain apply, few workgroups in flight keep the writes together:
+// below one entry in 25 words kDecApplyLds leaves two per CU, above it the
+// four that fit.  Activating an artifact over 4.02 G words at 0.1 / 1 / 10%,
+// and at 1% with 80% of the changes in 5% of the rows, takes 539 / 1757 /
+// 4643 / 963 us; with four per CU 536 / 1814 / 4643 / 974, with two 10% 5442;
+// decoding byte by byte, each wavefront storing 4 KiB of code on its own, 597
+// / 1944 / 6300 / 1190.
+constexpr size_t kDecApplyLds = 15 * 1024;
 __global__ __launch_bounds__(kLebThreads) void dec_apply_kernel(DecArgs a, bool aligned) {
   __shared__ __align__(16) uint8_t s_bytes[kDecBack + kDecTile];
   __shared__ uint64_t s_lo[kSegLds];
-  __shared__ uint32_t s_wterm[kLebWaves];
-  __shared__ uint64_t s_carry;
-  __shared__ uint64_t s_out[kLebWaves][kDecStepEntries];
-  const uint64_t tile = blockIdx.x;
+  __shared__ WaveOut s_out[kLebWaves];
+  __shared__ uint64_t s_run[kLebWaves];
+  __shared__ uint32_t s_n[kLebWaves];
+  const uint64_t tile = xcd_block(blockIdx.x, gridDim.x);
   if (tile == 0 && threadIdx.x == 0 && *a.d_count != a.capacity) raise_flag(a.err);
   const uint32_t terms = a.tile_terms[tile];
   if (terms == 0) return;   // uniform
-  const uint64_t b0 = tile * kDecTile;
   const DecTileRec rec = a.tile_recs[tile];
-  dec_load_tile(a, b0, aligned, s_bytes);                                    // barrier
-  const uint64_t e0 = rec.e0;
-  if (e0 >= a.capacity) {   // uniform: no value for any entry of this tile
+  if (rec.e0 >= a.capacity) {   // uniform: no value for any entry of this tile
     if (threadIdx.x == 0) raise_flag(a.err);
     return;
   }
   const uint32_t lane = lane_id(), wave = wave_id();
-  if (threadIdx.x < 64) {   // index of the entry just before the tile
-    const uint64_t g = tile / kTilesPerGroup;
-    uint32_t f;
-    uint64_t v;
-    seg_fold_tiles(a.tile_f, a.tile_v, g * kTilesPerGroup, tile, f, v);
-    if (threadIdx.x == 0) s_carry = f ? v : a.gexcl_v[g] + v;
-  }
-  const uint32_t wt = dec_wave_terms(s_bytes, b0, a.nbytes);
-  if (lane == 0) s_wterm[wave] = wt;
-  const TileSegs c = dec_tile_segs(a, rec, s_lo);
-  __syncthreads();
-  const uint64_t ew = dec_wave_e0(e0, s_wterm);
-  uint64_t run = s_carry;
-  for (uint32_t w = 0; w < wave; ++w)
-    run = a.wave_f[tile * kLebWaves + w] ? a.wave_v[tile * kLebWaves + w]
-                                         : run + a.wave_v[tile * kLebWaves + w];
+  const WaveBases<kDecApplyBases> wb(a.tbases, a.num_tensors);
   const uint64_t total = a.tbases[a.num_tensors];
-  bool bad = false;
-  uint32_t t = 0;                 // the tensor [lo, hi) last written by this lane
+  const uint64_t run = dec_wave_carry(a, tile, dec_tile_carry(a, tile));
+  uint32_t n;
+  if (!rec.generic) {   // uniform
+    n = dec_wave_short(a, tile, s_out[wave]);
+  } else {
+    dec_load_tile(a, tile * kDecTile, aligned, s_bytes);   // barrier
+    const TileSegs c = dec_tile_segs(a, rec, s_lo);
+    __syncthreads();
+    n = dec_wave_generic(a, c, s_lo, s_bytes, tile, dec_wave_e0(a, tile, rec.e0), run,
+                         s_out[wave]);
+  }
+  if (lane == 0) {
+    s_n[wave] = n;
+    s_run[wave] = run;
+  }
+  __syncthreads();
+  uint32_t off[kLebWaves + 1];   // each wavefront's first entry in the tile
+  off[0] = 0;
+#pragma unroll
+  for (int w = 0; w < kLebWaves; ++w) off[w + 1] = off[w] + s_n[w];
+  const uint32_t N = off[kLebWaves];
+  const auto index_of = [&](uint32_t i) {   // i < N
+    uint32_t w = 0, o = 0;
+#pragma unroll
+    for (int x = 1; x < kLebWaves; ++x) {
+      w = i >= off[x] ? x : w;
+      o = i >= off[x] ? off[x] : o;
+    }
+    return rec.generic ? s_out[w].idx[i - o] : s_run[w] + s_out[w].off[i - o];
+  };
+  constexpr int kPer = kDecWaveEntries / 64;
+  uint16_t v[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const uint32_t i = threadIdx.x + kLebThreads * u;
+    v[u] = (i < N && rec.e0 + i < a.capacity) ? a.val[rec.e0 + i] : 0;
+  }
+  // the tensor [lo, hi) of this lane's last entry, at first that of the
+  // wavefront's first
+  const uint32_t i0 = threadIdx.x - lane;
+  const uint32_t t0 = wb.tensor(a.tbases, a.num_tensors, i0 < N ? index_of(i0) : 0);
   uint64_t lo = 1, hi = 0;
-  uint16_t* base_ptr = nullptr;
-  uint64_t* so = s_out[wave];
-  uint64_t e = ew;
-  for (int it = 0; it < kDecSteps; ++it) {
-    const uint64_t e_step = e;
-    LaneDec d;
-    dec_lane_step(a, s_bytes, b0, it, e, d, bad);
-    uint32_t lf;
-    uint64_t lv;
-    lane_fold(a, c, s_lo, d, lf, lv);
-    uint32_t sf = lf;
-    uint64_t sv = lv;
-    wave_seg_scan(sf, sv);
-    uint32_t xf = __shfl_up(sf, 1);
-    uint64_t xv = __shfl_up(sv, 1);
-    if (lane == 0) {
-      xf = 0;
-      xv = 0;
-    }
-    uint64_t y = xf ? xv : run + xv;
-    const uint32_t f63 = __shfl(sf, 63);
-    const uint64_t v63 = __shfl(sv, 63);
-    run = f63 ? v63 : run + v63;
-    if (d.ends) {
-      SegCursor r = seg_cursor(a.segs, c, s_lo, d.e);
-      uint64_t k = d.e;
-      if (!lane_opens(a.segs, r, d)) {   // the common case: running sums
+  uint16_t* base = nullptr;
+  if (a.num_tensors) {
+    lo = a.tbases[t0];
+    hi = a.tbases[t0 + 1];
+    base = a.ptrs[t0];
+  }
+  bool bad = false;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          if ((d.ends >> j) & 1u) {
-            y += d.num[j];
-            so[k - e_step] = y;
-            ++k;
-          }
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          if ((d.ends >> j) & 1u) {
-            int64_t base;
-            y = seg_step(a.segs, c, s_lo, r, k, base) ? d.num[j] + (uint64_t)base : y + d.num[j];
-            so[k - e_step] = y;
-            ++k;
-          }
-        }
+  for (int u = 0; u < kPer; ++u) {
+    const uint32_t i = threadIdx.x + kLebThreads * u;
+    if (i >= N) continue;
+    const uint64_t y = index_of(i);
+    if (rec.e0 + i < a.capacity && y < total) {
+      if (!(y >= lo && y < hi)) {
+        const uint32_t t = find_tensor(a.tbases, a.num_tensors, y);
+        lo = a.tbases[t];
+        hi = a.tbases[t + 1];
+        base = a.ptrs[t];
       }
+      store_word<false>(base + (y - lo), v[u]);
+    } else {
+      bad = true;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const uint32_t n = (uint32_t)(e - e_step);
-    for (uint32_t i = lane; i < n; i += 64) {
-      const uint64_t k = e_step + i;
-      const uint64_t yi = so[i];
-      if (k < a.capacity && yi < total) {
-        if (!(yi >= lo && yi < hi)) {
-          t = dec_find_tensor(a.tbases, a.num_tensors, yi);
-          lo = a.tbases[t];
-          hi = a.tbases[t + 1];
-          base_ptr = a.ptrs[t];
-        }
-        __builtin_nontemporal_store(a.val[k], base_ptr + (yi - lo));
-      } else {
-        bad = true;
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();   // so[] is rewritten by the next step
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
   if (bad) raise_flag(a.err);
 }
@@ -1192,7 +1234,8 @@ DecLayout dec_layout(uint64_t nbytes) {
   L.tile_v = align_up(L.tile_f + 4 * bt);
   L.wave_f = align_up(L.tile_v + 8 * bt);
   L.wave_v = align_up(L.wave_f + 4 * kLebWaves * bt);
-  L.gsum_f = align_up(L.wave_v + 8 * kLebWaves * bt);
+  L.wave_t = align_up(L.wave_v + 8 * kLebWaves * bt);
+  L.gsum_f = align_up(L.wave_t + 2 * kLebWaves * bt);
   L.gsum_v = align_up(L.gsum_f + 4 * gb);
   L.gexcl_v = align_up(L.gsum_v + 8 * gb);
   L.tile_recs = align_up(L.gexcl_v + 8 * gb);
@@ -1265,10 +1308,11 @@ hipError_t launch_leb128_decode(DecArgs a, const DecLayout& L, char* ws, hipStre
   a.tile_v = (uint64_t*)(ws + L.tile_v);
   a.wave_f = (uint32_t*)(ws + L.wave_f);
   a.wave_v = (uint64_t*)(ws + L.wave_v);
+  a.wave_t = (uint16_t*)(ws + L.wave_t);
   a.gexcl_v = (uint64_t*)(ws + L.gexcl_v);
   const bool aligned = ((uintptr_t)a.in & 15u) == 0;
   const dim3 grid((uint32_t)L.btiles), block(kLebThreads);
-  hipLaunchKernelGGL(dec_count_kernel, grid, block, 0, stream, a, aligned);
+  hipLaunchKernelGGL(dec_sum_kernel, grid, block, 0, stream, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_group_scan(a.tile_terms, L.btiles, (uint64_t*)(ws + L.group_sum), a.group_excl,
                              a.d_count, stream)) != hipSuccess)
@@ -1289,7 +1333,8 @@ hipError_t launch_leb128_decode(DecArgs a, const DecLayout& L, char* ws, hipStre
                      a.gexcl_v, (uint64_t*)nullptr);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (apply)
-    hipLaunchKernelGGL(dec_apply_kernel, grid, block, 0, stream, a, aligned);
+    hipLaunchKernelGGL(dec_apply_kernel, grid, block, a.capacity < a.words / 25 ? kDecApplyLds : 0,
+                       stream, a, aligned);
   else
     hipLaunchKernelGGL(dec_write_kernel, grid, block, 0, stream, a, aligned);
   return hipGetLastError();
