@@ -3,18 +3,32 @@
 // deltas in order.  Apply assigns, so the chain equals one delta holding
 // every index of the chain with the value of the newest delta that has it.
 //
-// Two deltas A (older) and B (newer) merge with a merge path (Green,
-// McColl and Bader, "GPU merge path", 2012): workgroup t takes the merged
-// positions [4096 t, 4096 t + 4096); where every tile starts in A and B is
-// found first by one binary search on the diagonal per tile boundary (one
-// thread each), the workgroup stages both pieces in LDS, and each thread
-// merges 16 positions.  Ties put A first; an A entry whose
-// index B also holds is dropped (B's value wins).  A count pass, the group
-// scan of the per-tile counts, and a write pass give the compacted output.
-// Longer chains merge pairwise in rounds (a tree), with every count kept
-// on the device, so a whole composition is enqueued without a host wait.
+// Up to eight deltas (runs, oldest first) merge in one round, tile by tile.
+// A tile is a range of index values.  Its bounds come from samples: every
+// S-th index of every run, in merged order, of which each m-th (m = runs) is
+// a bound.  Runs of one density then put m S entries in every tile, whatever
+// their phase; whatever their densities, no tile holds more than (m + runs) S.
+// A split kernel (one thread per sample) ranks the samples by binary searches
+// among the other runs' samples and finds each bound's place in every run.
+// A workgroup loads its tile once into LDS, as 32-bit offsets from the
+// tile's first value, and merges its runs there pairwise, level by level
+// (merge path: Green, McColl and Bader, "GPU merge path", 2012; ties put the
+// older run first), each thread kPer outputs per level, held in registers
+// between the levels.  An entry is kept if the next one in the merged order
+// has another index.  A count pass, the group scan of the per-tile counts,
+// and a write pass give the compacted output; longer chains take further
+// rounds, with every count kept on the device, so a whole composition is
+// enqueued without a host wait.
+//
+// Bound by memory: a round reads every index twice and every word once and
+// writes what is kept, 28 bytes an entry in all; merging pairs in rounds moved
+// that once per round.  Chains of 1% deltas, against pairs in rounds (ms): 2 /
+// 4 over 4.02 G words (80 / 160 M entries) 0.53 / 1.24 against 0.80 / 2.89;
+// 5 / 8 over 1 G words 0.69 / 1.06 against 1.36 / 2.40; 12 over 300 M (two
+// rounds) 0.92 against 1.69.
 #include <string.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "delta_internal.h"
@@ -22,138 +36,140 @@
 namespace aurora {
 
 constexpr int kCmpThreads = 256;
-constexpr int kCmpPer = 16;                          // merged positions per thread
-constexpr int kCmpTile = kCmpThreads * kCmpPer;      // 4096
-constexpr int kCmpLoad = 8;                          // staging loads in flight per thread
+constexpr int kCmpPer = 15;                 // merged positions per thread (odd: LDS banks)
+constexpr int kCmpRuns = 8;                 // runs merged in one round, at most
+// A thread's positions lie in one pair of lists, so up to kCmpRuns / 2 pairs
+// may each leave a thread's share of positions unused.
+constexpr uint32_t kCmpCap = (kCmpThreads - kCmpRuns / 2) * kCmpPer;   // 3780 entries a tile holds
+// Entries an even tile holds: below the cap by about 5 standard deviations of
+// the runs' counts in a range of values.
+constexpr uint32_t kCmpTile = 3520;
 
+struct CmpRun {
+  const int64_t* idx;
+  const uint16_t* val;
+  uint64_t n;              // entries, or the most there can be if d_n is set
+  const uint64_t* d_n;     // nullable: the count in device memory
+};
 struct ComposeArgs {
-  const int64_t* a_idx;
-  const uint16_t* a_val;
-  uint64_t na;             // entries of A, or the most there can be if d_na is set
-  const uint64_t* d_na;    // nullable: A's count in device memory
-  const int64_t* b_idx;
-  const uint16_t* b_val;
-  uint64_t nb;
-  const uint64_t* d_nb;
+  CmpRun run[kCmpRuns];    // oldest first; past `runs` empty
+  uint32_t runs;
+  uint32_t step;           // S: entries between samples of a run
   int64_t* out_idx;
   uint16_t* out_val;
   uint64_t capacity;
   uint32_t* tile_counts;
   uint64_t* group_excl;
-  uint64_t* splits;        // entries of A before each tile boundary (tiles + 1)
+  uint64_t* pos;           // [tiles + 1][runs]: entries of each run before each tile
+  int64_t* bound;          // [tiles + 1]: least index of each tile; at the end the largest of all
   uint32_t* err;           // nullable: set when the merge meets unsorted input
 };
 
-__device__ __forceinline__ uint64_t live_count(uint64_t n, const uint64_t* d_n) {
-  if (!d_n) return n;
-  const uint64_t c = *d_n;
-  return c < n ? c : n;
+__device__ __forceinline__ void cmp_flag(const ComposeArgs& a) {
+  if (a.err) __hip_atomic_fetch_or(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Merged position d -> entries of A before it (ties: A first).  Always in
-// [max(0, d - nb), min(d, na)].
-template <typename GetA, typename GetB>
-__device__ __forceinline__ uint64_t diag_split(GetA A, GetB B, uint64_t na, uint64_t nb,
-                                               uint64_t d) {
-  uint64_t lo = d > nb ? d - nb : 0, hi = d < na ? d : na;
-  while (lo < hi) {
-    const uint64_t mid = (lo + hi) >> 1;
-    if (A(mid) <= B(d - mid - 1)) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
-
-// splits[b] = entries of A before merged position min(b * kCmpTile, na + nb),
-// one thread per tile boundary.
-__global__ void compose_split_kernel(ComposeArgs a, uint64_t num_bounds) {
-  const uint64_t b = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= num_bounds) return;
-  const uint64_t na = live_count(a.na, a.d_na), nb = live_count(a.nb, a.d_nb);
-  const uint64_t total = na + nb;
-  const uint64_t d = b * kCmpTile < total ? b * kCmpTile : total;
-  auto A = [&](uint64_t i) { return a.a_idx[i]; };
-  auto B = [&](uint64_t j) { return a.b_idx[j]; };
-  a.splits[b] = diag_split(A, B, na, nb, d);
-}
-
-// One tile of the merge: its bounds in A and B, staged in LDS.
-struct CmpTile {
-  uint64_t i0, j0;      // first entries of A and B in the tile
-  uint32_t la, lb;      // entries of A and B in the tile
-  uint32_t positions;   // merged positions of the tile
-  bool ext;             // s_b[lb] holds B's next entry (for the duplicate test)
-  bool ok;
-};
-
-// Block-wide (a barrier after the staging).  Returns ok = false for a tile
-// past the end or for inconsistent (unsorted) input.
-__device__ __forceinline__ CmpTile cmp_load_tile(const ComposeArgs& a, uint64_t tile,
-                                                 uint64_t na, uint64_t nb, int64_t* s_ab) {
-  CmpTile t{};
-  const uint64_t d0 = tile * kCmpTile;
-  const uint64_t total = na + nb;
-  if (d0 >= total) return t;   // uniform
-  const uint64_t d1 = d0 + kCmpTile < total ? d0 + kCmpTile : total;
-  const uint64_t i0 = a.splits[tile], i1 = a.splits[tile + 1];
-  const uint64_t j0 = d0 - i0, j1 = d1 - i1;
-  if (i1 < i0 || j1 < j0 || i0 > d0 || i1 > d1) {   // only unsorted input gets here
-    if (threadIdx.x == 0 && a.err)
-      __hip_atomic_fetch_or(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return t;
-  }
-  t.i0 = i0;
-  t.j0 = j0;
-  t.la = (uint32_t)(i1 - i0);
-  t.lb = (uint32_t)(j1 - j0);
-  t.positions = (uint32_t)(d1 - d0);
-  t.ext = j1 < nb;
-  const uint32_t nload = t.la + t.lb + (t.ext ? 1u : 0u);
-  // kCmpLoad loads per thread in flight before any LDS store
-  for (uint32_t q0 = 0; q0 < nload; q0 += kCmpThreads * kCmpLoad) {
-    int64_t v[kCmpLoad];
+// Live sizes of the runs; returns the number of samples.
+template <int G>
+__device__ __forceinline__ uint64_t cmp_sizes(const ComposeArgs& a, uint64_t (&n)[G]) {
+  uint64_t samples = 0;
 #pragma unroll
-    for (int k = 0; k < kCmpLoad; ++k) {
-      const uint32_t q = q0 + threadIdx.x + kCmpThreads * k;
-      v[k] = q < nload ? (q < t.la ? a.a_idx[i0 + q] : a.b_idx[j0 + (q - t.la)]) : 0;
+  for (int k = 0; k < G; ++k) {
+    n[k] = k < (int)a.runs ? a.run[k].n : 0;
+    if (k < (int)a.runs && a.run[k].d_n) {
+      const uint64_t c = *a.run[k].d_n;
+      n[k] = c < n[k] ? c : n[k];
     }
-#pragma unroll
-    for (int k = 0; k < kCmpLoad; ++k) {
-      const uint32_t q = q0 + threadIdx.x + kCmpThreads * k;
-      if (q < nload) s_ab[q] = v[k];
-    }
+    samples += (n[k] + a.step - 1) / a.step;
   }
-  __syncthreads();
-  t.ok = true;
-  return t;
+  return samples;
 }
 
-// Walks this thread's merged positions; emit(index, from_b, position in
-// its tile piece) is called for every kept entry, in order.
-template <typename Emit>
-__device__ __forceinline__ void cmp_walk(const CmpTile& t, const int64_t* s_ab, uint64_t nb,
-                                         Emit emit) {
-  const int64_t* sA = s_ab;
-  const int64_t* sB = s_ab + t.la;
-  const uint32_t p0 = threadIdx.x * kCmpPer;
-  if (p0 >= t.positions) return;
-  uint32_t lo = p0 > t.lb ? p0 - t.lb : 0, hi = p0 < t.la ? p0 : t.la;
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (sA[mid] <= sB[p0 - mid - 1]) lo = mid + 1; else hi = mid;
+// One thread per sample (the first of run 0, of run 1, ..., then the second
+// of each, would scatter the reads: samples go run by run) and one for the
+// end.  The searches of one thread, one per run, advance in step, so that
+// their loads are in flight together.
+template <int G>
+__global__ __launch_bounds__(256) void compose_split_kernel(ComposeArgs a) {
+  uint64_t n[G];
+  const uint64_t samples = cmp_sizes<G>(a, n);
+  const uint64_t m = a.runs, S = a.step;
+  const uint64_t tiles = (samples + m - 1) / m;
+  uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i > samples || samples == 0) return;
+  if (i == samples) {   // the end of the last tile
+    int64_t top = INT64_MIN;
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      if (k < (int)a.runs) a.pos[tiles * m + k] = n[k];
+      if (n[k]) {
+        const int64_t x = a.run[k].idx[n[k] - 1];
+        top = x > top ? x : top;
+      }
+    }
+    a.bound[tiles] = top;
+    return;
   }
-  uint32_t i = lo, j = p0 - lo;
-  const uint32_t n = t.positions - p0 < (uint32_t)kCmpPer ? t.positions - p0 : kCmpPer;
-  for (uint32_t s = 0; s < n; ++s) {
-    if (i < t.la && (j >= t.lb || sA[i] <= sB[j])) {
-      // dropped when B holds the same index (it comes right after)
-      const bool dup = t.j0 + j < nb && (j < t.lb || t.ext) && sB[j] == sA[i];
-      if (!dup) emit(sA[i], false, i);
-      ++i;
-    } else {
-      emit(sB[j], true, j);
-      ++j;
+  uint32_t own = 0;
+#pragma unroll
+  for (int k = 0; k + 1 < G; ++k) {
+    const uint64_t c = (n[k] + S - 1) / S;
+    if (own == (uint32_t)k && i >= c) {
+      i -= c;
+      own = k + 1;
     }
   }
+  const int64_t* src = a.run[0].idx;
+#pragma unroll
+  for (int k = 1; k < G; ++k) src = own == (uint32_t)k ? a.run[k].idx : src;
+  const int64_t x = src[i * S];
+  // samples of each other run before x: at most x in older runs, below it
+  // in newer ones
+  uint64_t lo[G], hi[G];
+  uint64_t widest = 0;
+#pragma unroll
+  for (int k = 0; k < G; ++k) {
+    lo[k] = 0;
+    hi[k] = own == (uint32_t)k ? 0 : (n[k] + S - 1) / S;
+    widest = hi[k] > widest ? hi[k] : widest;
+  }
+  for (; widest; widest >>= 1) {   // every interval is at most `widest` long
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      if (lo[k] < hi[k]) {
+        const uint64_t mid = (lo[k] + hi[k]) >> 1;
+        const int64_t y = a.run[k].idx[mid * S];
+        if (y < x || (y == x && (uint32_t)k < own)) lo[k] = mid + 1; else hi[k] = mid;
+      }
+    }
+  }
+  uint64_t rank = i;
+#pragma unroll
+  for (int k = 0; k < G; ++k) rank += lo[k];
+  if (rank % m) return;
+  const uint64_t t = rank / m;
+  // where x falls in every run: after the last sample counted, at most at
+  // the one after it
+#pragma unroll
+  for (int k = 0; k < G; ++k) {
+    const uint64_t c = lo[k];
+    lo[k] = c ? (c - 1) * S : 0;
+    hi[k] = c * S < n[k] ? c * S : n[k];
+    if (own == (uint32_t)k) lo[k] = hi[k] = i * S;
+  }
+  for (uint64_t w = S; w; w >>= 1) {
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      if (lo[k] < hi[k]) {
+        const uint64_t mid = (lo[k] + hi[k]) >> 1;
+        if (a.run[k].idx[mid] < x) lo[k] = mid + 1; else hi[k] = mid;
+      }
+    }
+  }
+  a.bound[t] = x;
+#pragma unroll
+  for (int k = 0; k < G; ++k)
+    if (k < (int)a.runs) a.pos[t * m + k] = lo[k];
 }
 
 __device__ __forceinline__ uint32_t cmp_block_sum(uint32_t v, uint32_t* s_wave) {
@@ -168,166 +184,377 @@ __device__ __forceinline__ uint32_t cmp_block_sum(uint32_t v, uint32_t* s_wave) 
   return t;
 }
 
-__global__ __launch_bounds__(kCmpThreads) void compose_count_kernel(ComposeArgs a) {
-  __shared__ int64_t s_ab[kCmpTile + 1];
-  __shared__ uint32_t s_wave[kCmpThreads / 64];
-  const uint64_t na = live_count(a.na, a.d_na), nb = live_count(a.nb, a.d_nb);
-  const CmpTile t = cmp_load_tile(a, blockIdx.x, na, nb, s_ab);
-  uint32_t kept = 0;
-  if (t.ok) cmp_walk(t, s_ab, nb, [&](int64_t, bool, uint32_t) { ++kept; });
-  const uint32_t total = cmp_block_sum(kept, s_wave);
-  if (threadIdx.x == 0) a.tile_counts[blockIdx.x] = total;
-}
+// What a workgroup holds of its tile at a time: a window of entries of every
+// run (the whole tile, unless it holds more than kCmpCap entries or spans
+// 2^32 index values).
+template <int G>
+struct CmpWindow {
+  int64_t base;        // offsets count from this index
+  uint32_t off[G + 1]; // each run's first entry in the window, and the end
+};
 
-// Write pass: the walk keeps each thread's merged entries in registers, the
-// tile's kept entries are assembled in LDS (over the staged input), and the
-// workgroup stores them as one contiguous, coalesced run.
-__global__ __launch_bounds__(kCmpThreads) void compose_write_kernel(ComposeArgs a) {
-  __shared__ int64_t s_ab[kCmpTile + 1];
-  __shared__ uint16_t s_vab[kCmpTile];
+constexpr uint32_t kCmpNone = 0xFFFFFFFFu;     // no key: past a list's end
+constexpr uint64_t kCmpSpan = 0xFFFFFFFEull;   // keys are below this
+
+// The count pass needs no order: a tile that spans at most kCmpBits values is
+// counted by a bit per value (an entry whose bit is already set is a
+// duplicate): 369 against 551 us for four runs of 40 M entries.  24 KB of bits
+// leave six workgroups on a CU; with 32 KB the composition takes 1374 us
+// instead of 1243, with 16 KB the bits are too few for two 1% deltas (570
+// against 532 us).
+constexpr uint32_t kCmpBits = 32 * 6144;
+
+// The launch bound's wavefronts per SIMD: four runs composed with the write
+// pass at 3 / 4 / 5 1571 / 1481 / 1793 us; the count pass at 4 / 6 1481 / 1476
+// us, eight runs 1214 / 1319.
+template <int G, bool kWrite>
+__global__ __launch_bounds__(kCmpThreads, kWrite || G == 8 ? 4 : 6) void compose_tile_kernel(
+    ComposeArgs a) {
+  __shared__ uint32_t s_key[kWrite ? kCmpCap : kCmpBits / 32];
+  __shared__ uint16_t s_val[kWrite ? kCmpCap : 1];
+  __shared__ uint64_t s_cur[G], s_end[G];
+  __shared__ int64_t s_head[G], s_next[G];
+  __shared__ uint32_t s_take[G];
   __shared__ uint32_t s_wave[kCmpThreads / 64];
   __shared__ uint64_t s_before;
-  const uint64_t na = live_count(a.na, a.d_na), nb = live_count(a.nb, a.d_nb);
+  const uint32_t runs = a.runs;
+  uint64_t n_run[G];
+  const uint64_t samples = cmp_sizes<G>(a, n_run);
+  const uint64_t tiles = (samples + runs - 1) / runs;
   const uint64_t tile = blockIdx.x;
-  const CmpTile t = cmp_load_tile(a, tile, na, nb, s_ab);
-  if (!t.ok) return;   // uniform
-  for (uint32_t q0 = 0; q0 < t.la + t.lb; q0 += kCmpThreads * kCmpLoad) {
-    uint16_t v[kCmpLoad];
+  if (tile >= tiles) {   // uniform
+    if (!kWrite && threadIdx.x == 0) a.tile_counts[tile] = 0;
+    return;
+  }
+  bool bad = false;
+  const int64_t v0 = a.bound[tile];
+  const bool last_tile = tile + 1 == tiles;
+  const int64_t v1 = a.bound[tile + 1];
+  const uint64_t span = (uint64_t)v1 - (uint64_t)v0 + (last_tile ? 1 : 0);   // values of the tile
+  if (threadIdx.x < G) {
+    const uint32_t k = threadIdx.x;
+    uint64_t p0 = 0, p1 = 0;
+    if (k < runs) {
+      p0 = a.pos[tile * runs + k];
+      p1 = a.pos[(tile + 1) * runs + k];
+      uint64_t n = 0;
 #pragma unroll
-    for (int k = 0; k < kCmpLoad; ++k) {
-      const uint32_t q = q0 + threadIdx.x + kCmpThreads * k;
-      v[k] = q < t.la + t.lb ? (q < t.la ? a.a_val[t.i0 + q] : a.b_val[t.j0 + (q - t.la)]) : 0;
+      for (int j = 0; j < G; ++j) n = k == (uint32_t)j ? n_run[j] : n;
+      // Only unsorted input (whose samples may leave a bound unwritten) fails
+      // this: a sorted run has at most 2 S runs entries between two bounds.
+      if (p1 > n || p0 > p1 || p1 - p0 > 2ull * runs * a.step) {
+        bad = true;
+        p0 = p1 = 0;
+      }
     }
+    s_cur[k] = p0;
+    s_end[k] = p1;
+  }
+  if (kWrite && threadIdx.x >= 64 && threadIdx.x < 128) {   // kept by the group's earlier tiles
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t g0 = tile / kTilesPerGroup * kTilesPerGroup;
+    uint64_t c = g0 + lane < tile ? (uint64_t)a.tile_counts[g0 + lane] : 0;
 #pragma unroll
-    for (int k = 0; k < kCmpLoad; ++k) {
-      const uint32_t q = q0 + threadIdx.x + kCmpThreads * k;
-      if (q < t.la + t.lb) s_vab[q] = v[k];
-    }
+    for (int s = 32; s >= 1; s >>= 1) c += __shfl_xor(c, s);
+    if (lane == 0) s_before = a.group_excl[tile / kTilesPerGroup] + c;
   }
   __syncthreads();
-  // merged position s of this thread: oi[s], ov[s]; bit s of keep: kept
-  int64_t oi[kCmpPer];
-  uint16_t ov[kCmpPer];
-  uint32_t keep = 0;
-  {
-    const int64_t* sA = s_ab;
-    const int64_t* sB = s_ab + t.la;
-    const uint32_t p0 = threadIdx.x * kCmpPer;
-    uint32_t i = 0, j = 0, n = 0;
-    if (p0 < t.positions) {
-      uint32_t lo = p0 > t.lb ? p0 - t.lb : 0, hi = p0 < t.la ? p0 : t.la;
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (sA[mid] <= sB[p0 - mid - 1]) lo = mid + 1; else hi = mid;
-      }
-      i = lo;
-      j = p0 - lo;
-      n = t.positions - p0 < (uint32_t)kCmpPer ? t.positions - p0 : kCmpPer;
-    }
+  uint64_t out = kWrite ? s_before : 0;   // kept entries before the window
+  bool first_window = true;
+  while (true) {
+    CmpWindow<G> w;
+    uint64_t cur[G], left = 0;
 #pragma unroll
-    for (uint32_t s = 0; s < (uint32_t)kCmpPer; ++s) {
-      oi[s] = 0;
-      ov[s] = 0;
-      if (s < n) {
-        if (i < t.la && (j >= t.lb || sA[i] <= sB[j])) {
-          // dropped when B holds the same index (it comes right after)
-          const bool dup = (j < t.lb || t.ext) && sB[j] == sA[i];
-          oi[s] = sA[i];
-          ov[s] = s_vab[i];
-          keep |= (uint32_t)!dup << s;
-          ++i;
-        } else {
-          oi[s] = sB[j];
-          ov[s] = s_vab[t.la + j];
-          keep |= 1u << s;
-          ++j;
+    for (int k = 0; k < G; ++k) {
+      cur[k] = s_cur[k];
+      left += s_end[k] - cur[k];
+    }
+    if (left == 0) break;   // uniform
+    w.off[0] = 0;
+    const bool whole = left <= kCmpCap && first_window && span - 1 < kCmpSpan;
+    if (whole) {
+      w.base = v0;
+#pragma unroll
+      for (int k = 0; k < G; ++k) w.off[k + 1] = w.off[k] + (uint32_t)(s_end[k] - cur[k]);
+    } else {
+      // at most kCmpCap / runs entries of every run, of them those below the
+      // first one left out of any run, and below kCmpSpan from the least
+      const uint64_t quota = kCmpCap / runs;
+      if (threadIdx.x < runs) {
+        const uint32_t k = threadIdx.x;
+        const uint64_t c = s_cur[k], r = s_end[k] - c;
+        s_head[k] = r ? a.run[k].idx[c] : INT64_MAX;
+        s_next[k] = r > quota ? a.run[k].idx[c + quota] : INT64_MAX;
+      }
+      __syncthreads();
+      int64_t cut = INT64_MAX;
+      w.base = INT64_MAX;
+      for (uint32_t k = 0; k < runs; ++k) {
+        w.base = s_head[k] < w.base ? s_head[k] : w.base;
+        cut = s_next[k] < cut ? s_next[k] : cut;
+      }
+      // INT64_MAX may be an index: with no entry left out there is no cut
+      bool none_out = true;
+#pragma unroll
+      for (int k = 0; k < G; ++k) none_out = none_out && s_end[k] - cur[k] <= quota;
+      uint64_t width = none_out ? kCmpSpan : (uint64_t)cut - (uint64_t)w.base;
+      width = width < kCmpSpan ? width : kCmpSpan;
+      if (threadIdx.x < runs) {
+        const uint32_t k = threadIdx.x;
+        const uint64_t c = s_cur[k], r = s_end[k] - c;
+        uint64_t lo = 0, hi = r < quota ? r : quota;
+        while (lo < hi) {
+          const uint64_t mid = (lo + hi) >> 1;
+          if ((uint64_t)a.run[k].idx[c + mid] - (uint64_t)w.base < width) lo = mid + 1; else hi = mid;
+        }
+        s_take[k] = (uint32_t)lo;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < G; ++k) w.off[k + 1] = w.off[k] + (k < (int)runs ? s_take[k] : 0u);
+      if (w.off[G] == 0) {   // uniform; only unsorted input gets here
+        bad = true;
+        break;
+      }
+    }
+    first_window = false;
+    const uint32_t total = w.off[G];
+    {
+      int64_t x[kCmpPer];
+      uint16_t v[kWrite ? kCmpPer : 1];
+#pragma unroll
+      for (int u = 0; u < kCmpPer; ++u) {
+        const uint32_t q = threadIdx.x + kCmpThreads * u;
+        const int64_t* pi = a.run[0].idx + cur[0];
+        const uint16_t* pv = a.run[0].val + cur[0];
+#pragma unroll
+        for (int k = 1; k < G; ++k) {
+          pi = q >= w.off[k] ? a.run[k].idx + cur[k] - w.off[k] : pi;
+          if (kWrite) pv = q >= w.off[k] ? a.run[k].val + cur[k] - w.off[k] : pv;
+        }
+        x[u] = q < total ? pi[q] : 0;
+        if (kWrite) v[u] = q < total ? pv[q] : 0;
+      }
+      if (!kWrite && whole && span <= kCmpBits) {   // uniform
+        for (uint32_t i = threadIdx.x; i < (uint32_t)(span + 31) / 32; i += kCmpThreads) s_key[i] = 0;
+        __syncthreads();
+        uint32_t kept = 0;
+#pragma unroll
+        for (int u = 0; u < kCmpPer; ++u) {
+          const uint32_t q = threadIdx.x + kCmpThreads * u;
+          const uint64_t d = (uint64_t)x[u] - (uint64_t)w.base;
+          const int64_t before = __shfl_up((long long)x[u], 1);
+          bool opens = (threadIdx.x & 63) == 0;
+#pragma unroll
+          for (int k = 1; k < G; ++k) opens = opens || q == w.off[k];
+          if (q < total && ((!opens && before >= x[u]) || d >= span)) bad = true;
+          if (q < total && d < span) {
+            const uint32_t bit = 1u << (d & 31);
+            kept += (atomicOr(&s_key[d >> 5], bit) & bit) == 0;
+          }
+        }
+        out += cmp_block_sum(kept, s_wave);
+        break;
+      }
+#pragma unroll
+      for (int u = 0; u < kCmpPer; ++u) {
+        const uint32_t q = threadIdx.x + kCmpThreads * u;
+        if (q < total) {
+          const uint64_t d = (uint64_t)x[u] - (uint64_t)w.base;
+          if (d >= kCmpSpan) bad = true;   // only unsorted input
+          s_key[q] = d < kCmpSpan ? (uint32_t)d : (uint32_t)(kCmpSpan - 1);
+          if (kWrite) s_val[q] = v[u];
         }
       }
     }
-  }
-  const uint32_t kept = __builtin_popcount(keep);
-  // exclusive prefix of `kept` over the workgroup
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t x = kept;
+    __syncthreads();
+    if (!kWrite) {   // strictly increasing within a run
 #pragma unroll
-  for (int s = 1; s < 64; s <<= 1) {
-    const uint32_t y = __shfl_up(x, s);
-    if ((int)lane >= s) x += y;
-  }
-  if (lane == 63) s_wave[wave] = x;
-  if (threadIdx.x < 64) {   // kept entries of the group's tiles before this one
-    const uint64_t g0 = tile / kTilesPerGroup * kTilesPerGroup;
-    uint64_t c = g0 + threadIdx.x < tile ? (uint64_t)a.tile_counts[g0 + threadIdx.x] : 0;
+      for (int u = 0; u < kCmpPer; ++u) {
+        const uint32_t q = threadIdx.x + kCmpThreads * u;
+        bool opens = q == 0;
 #pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) c += __shfl_xor(c, s);
-    if (threadIdx.x == 0) s_before = c;
-  }
-  __syncthreads();   // also: every thread is done reading the staged input
-  uint32_t local = x - kept;
-  uint32_t tile_kept = 0;
-  for (int w = 0; w < kCmpThreads / 64; ++w) {
-    if (w < (int)wave) local += s_wave[w];
-    tile_kept += s_wave[w];
-  }
-#pragma unroll
-  for (uint32_t s = 0; s < (uint32_t)kCmpPer; ++s) {
-    if ((keep >> s) & 1u) {
-      s_ab[local] = oi[s];
-      s_vab[local] = ov[s];
-      ++local;
+        for (int k = 1; k < G; ++k) opens = opens || q == w.off[k];
+        if (q < total && !opens && s_key[q - 1] >= s_key[q]) bad = true;
+      }
     }
-  }
-  __syncthreads();
-  const uint64_t base = a.group_excl[tile / kTilesPerGroup] + s_before;
-  for (uint32_t q = threadIdx.x; q < tile_kept; q += kCmpThreads) {
-    if (base + q < a.capacity) {
-      a.out_idx[base + q] = s_ab[q];
-      a.out_val[base + q] = s_vab[q];
+    // Levels: lists of `width` runs merge into lists of 2 * width.
+    uint32_t key[kCmpPer];
+    uint16_t val[kWrite ? kCmpPer : 1];
+    uint32_t n = 0, at = 0, next = kCmpNone;
+#pragma unroll
+    for (int width = 1; width < G; width *= 2) {
+      // this thread's pair of lists and its first position in the merged pair
+      uint32_t t = threadIdx.x, la0 = 0, lb0 = 0, lb1 = 0;
+      bool found = false;
+#pragma unroll
+      for (int k = 0; k < G; k += 2 * width) {
+        const uint32_t b = w.off[k], m = w.off[k + width < G ? k + width : G];
+        const uint32_t e = w.off[k + 2 * width < G ? k + 2 * width : G];
+        const uint32_t threads = (e - b + kCmpPer - 1) / kCmpPer;
+        if (!found) {
+          if (t < threads) {
+            found = true;
+            la0 = b;
+            lb0 = m;
+            lb1 = e;
+          } else {
+            t -= threads;
+          }
+        }
+      }
+      n = 0;
+      if (found) {
+        const uint32_t p0 = t * kCmpPer, la = lb0 - la0, lb = lb1 - lb0;
+        uint32_t lo = p0 > lb ? p0 - lb : 0, hi = p0 < la ? p0 : la;
+        while (lo < hi) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (s_key[la0 + mid] <= s_key[lb0 + p0 - mid - 1]) lo = mid + 1; else hi = mid;
+        }
+        uint32_t i = la0 + lo, j = lb0 + p0 - lo;
+        at = la0 + p0;
+        n = la + lb - p0 < (uint32_t)kCmpPer ? la + lb - p0 : kCmpPer;
+        uint32_t x = i < lb0 ? s_key[i] : kCmpNone, y = j < lb1 ? s_key[j] : kCmpNone;
+#pragma unroll
+        for (int s = 0; s < kCmpPer; ++s) {
+          const bool older = x <= y;
+          key[s] = older ? x : y;
+          const uint32_t q = older ? i : j;
+          if (kWrite) val[s] = s < (int)n ? s_val[q] : 0;
+          const uint32_t z = q + 1 < (older ? lb0 : lb1) ? s_key[q + 1] : kCmpNone;
+          x = older ? z : x;
+          y = older ? y : z;
+          i += older ? 1u : 0u;
+          j += older ? 0u : 1u;
+        }
+        next = x < y ? x : y;
+      }
+      __syncthreads();   // every list of this level has been read
+      if (2 * width < G) {
+#pragma unroll
+        for (int s = 0; s < kCmpPer; ++s) {
+          if (s < (int)n) {
+            s_key[at + s] = key[s];
+            if (kWrite) s_val[at + s] = val[s];
+          }
+        }
+        __syncthreads();
+      }
     }
+    // kept: the next merged entry has another index
+    uint32_t keep = 0;
+#pragma unroll
+    for (int s = 0; s < kCmpPer; ++s) {
+      const uint32_t nx = s + 1 < kCmpPer ? key[s + 1 < kCmpPer ? s + 1 : s] : next;
+      if (s < (int)n && (s + 1 < (int)n || s + 1 == kCmpPer ? nx : kCmpNone) != key[s])
+        keep |= 1u << s;
+    }
+    const uint32_t kept = __builtin_popcount(keep);
+    if (!kWrite) {
+      out += cmp_block_sum(kept, s_wave);
+    } else {
+      const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+      uint32_t incl = kept;
+#pragma unroll
+      for (int s = 1; s < 64; s <<= 1) {
+        const uint32_t y = __shfl_up(incl, s);
+        if ((int)lane >= s) incl += y;
+      }
+      if (lane == 63) s_wave[wave] = incl;
+      __syncthreads();
+      uint32_t local = incl - kept, window = 0;
+#pragma unroll
+      for (int x = 0; x < kCmpThreads / 64; ++x) {
+        local += x < (int)wave ? s_wave[x] : 0u;
+        window += s_wave[x];
+      }
+#pragma unroll
+      for (int s = 0; s < kCmpPer; ++s) {
+        if ((keep >> s) & 1u) {
+          s_key[local] = key[s];
+          s_val[local] = val[s];
+          ++local;
+        }
+      }
+      __syncthreads();
+      for (uint32_t q = threadIdx.x; q < window; q += kCmpThreads) {
+        if (out + q < a.capacity) {
+          a.out_idx[out + q] = (int64_t)((uint64_t)w.base + s_key[q]);
+          a.out_val[out + q] = s_val[q];
+        }
+      }
+      out += window;
+    }
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int k = 0; k < G; ++k) s_cur[k] = cur[k] + (w.off[k + 1] - w.off[k]);
+    }
+    __syncthreads();   // s_cur is published; s_key, s_val and s_wave are free
   }
+  if (!kWrite && threadIdx.x == 0) a.tile_counts[tile] = (uint32_t)out;
+  if (bad) cmp_flag(a);
 }
 
-static uint64_t cmp_tiles(uint64_t n) { return (n + kCmpTile - 1) / kCmpTile; }
-
-// Scratch of one pairwise merge of up to n merged positions.
+// Scratch of one round's merge of `runs` runs of up to n entries in all.
 struct CmpScratch {
-  size_t tile_counts, group_sum, group_excl, splits, total;
+  uint64_t step, samples, tiles;   // at most
+  size_t tile_counts, group_sum, group_excl, pos, bound, total;
 };
-static CmpScratch cmp_scratch(uint64_t n) {
+static CmpScratch cmp_scratch(uint64_t n, uint64_t runs) {
   CmpScratch s;
-  const uint64_t tiles = cmp_tiles(n), groups = groups_for(tiles);
+  s.step = kCmpTile / runs;
+  s.samples = n / s.step + runs;
+  s.tiles = (s.samples + runs - 1) / runs;
+  const uint64_t groups = groups_for(s.tiles);
   s.tile_counts = 0;
-  s.group_sum = align_up(4 * tiles);
+  s.group_sum = align_up(4 * s.tiles);
   s.group_excl = align_up(s.group_sum + 8 * groups);
-  s.splits = align_up(s.group_excl + 8 * groups);
-  s.total = align_up(s.splits + 8 * (tiles + 1));
+  s.pos = align_up(s.group_excl + 8 * groups);
+  s.bound = align_up(s.pos + 8 * runs * (s.tiles + 1));
+  s.total = align_up(s.bound + 8 * (s.tiles + 1));
   return s;
 }
 
-static hipError_t launch_compose2(ComposeArgs a, char* scratch, uint64_t* d_count,
-                                  hipStream_t stream) {
-  const uint64_t tiles = cmp_tiles(a.na + a.nb);
-  if (tiles == 0) return launch_reset(d_count, nullptr, 0, stream);
-  const CmpScratch s = cmp_scratch(a.na + a.nb);
-  a.tile_counts = (uint32_t*)(scratch + s.tile_counts);
-  a.group_excl = (uint64_t*)(scratch + s.group_excl);
-  a.splits = (uint64_t*)(scratch + s.splits);
-  const uint64_t bounds = tiles + 1;
-  hipLaunchKernelGGL(compose_split_kernel, dim3((uint32_t)((bounds + 255) / 256)), dim3(256), 0,
-                     stream, a, bounds);
+template <int G>
+static hipError_t launch_merge(const ComposeArgs& a, const CmpScratch& s, uint64_t* group_sum,
+                               uint64_t* d_count, hipStream_t stream) {
+  hipLaunchKernelGGL(compose_split_kernel<G>, dim3((uint32_t)((s.samples + 1 + 255) / 256)),
+                     dim3(256), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(compose_count_kernel, dim3((uint32_t)tiles), dim3(kCmpThreads), 0, stream, a);
+  hipLaunchKernelGGL((compose_tile_kernel<G, false>), dim3((uint32_t)s.tiles), dim3(kCmpThreads), 0,
+                     stream, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  e = launch_group_scan(a.tile_counts, tiles, (uint64_t*)(scratch + s.group_sum), a.group_excl,
-                        d_count, stream);
+  e = launch_group_scan(a.tile_counts, s.tiles, group_sum, a.group_excl, d_count, stream);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(compose_write_kernel, dim3((uint32_t)tiles), dim3(kCmpThreads), 0, stream, a);
+  hipLaunchKernelGGL((compose_tile_kernel<G, true>), dim3((uint32_t)s.tiles), dim3(kCmpThreads), 0,
+                     stream, a);
   return hipGetLastError();
 }
 
+static hipError_t launch_compose_runs(ComposeArgs a, char* scratch, uint64_t* d_count,
+                                      hipStream_t stream) {
+  uint64_t n = 0;
+  for (uint32_t k = 0; k < a.runs; ++k) n += a.run[k].n;
+  if (n == 0) return launch_reset(d_count, nullptr, 0, stream);
+  const CmpScratch s = cmp_scratch(n, a.runs);
+  a.step = (uint32_t)s.step;
+  a.tile_counts = (uint32_t*)(scratch + s.tile_counts);
+  a.group_excl = (uint64_t*)(scratch + s.group_excl);
+  a.pos = (uint64_t*)(scratch + s.pos);
+  a.bound = (int64_t*)(scratch + s.bound);
+  uint64_t* group_sum = (uint64_t*)(scratch + s.group_sum);
+  if (a.runs <= 2) return launch_merge<2>(a, s, group_sum, d_count, stream);
+  if (a.runs <= 4) return launch_merge<4>(a, s, group_sum, d_count, stream);
+  return launch_merge<8>(a, s, group_sum, d_count, stream);
+}
+
 // ------------------------------------------------------------ the chain
+
+// Runs of a round over `items` runs: groups of neighbours, as even as can be
+// (a group of one is carried over).
+static uint64_t cmp_groups(uint64_t items) { return (items + kCmpRuns - 1) / kCmpRuns; }
 
 // Workspace: scratch of the largest merge, one count slot per delta, and
 // the intermediate results of every round but the last (each round's
@@ -337,11 +564,14 @@ ChainLayout chain_layout(const uint64_t* counts, int32_t K) {
   uint64_t total = 0;
   for (int32_t d = 0; d < K; ++d) total += counts[d];
   uint64_t rounds = 0;
-  for (int64_t items = K; items > 1; items = (items + 1) / 2) ++rounds;
+  for (uint64_t items = K > 0 ? K : 0; items > 1; items = cmp_groups(items)) ++rounds;
   if (K == 1) rounds = 1;   // one merge with an empty delta: a copy
   L.rounds = rounds;
   L.scratch = 0;
-  L.counts = align_up(cmp_scratch(total).total);
+  size_t scratch = 0;   // more runs mean shorter steps, and rows of more positions
+  for (uint64_t r = 2; r <= (uint64_t)kCmpRuns; ++r)
+    if (r == 2 || (int64_t)r <= K) scratch = std::max(scratch, cmp_scratch(total, r).total);
+  L.counts = align_up(scratch);
   L.inter = align_up(L.counts + 8 * (uint64_t)(K > 0 ? K : 1));
   const uint64_t inter_rounds = rounds > 1 ? rounds - 1 : 0;
   L.total = align_up(L.inter + inter_rounds * (align_up(8 * total) + align_up(2 * total)));
@@ -356,41 +586,35 @@ hipError_t launch_compose_chain(const int64_t* const* idx, const uint16_t* const
   const ChainLayout L = chain_layout(counts, K);
   uint64_t total = 0;
   for (int32_t d = 0; d < K; ++d) total += counts[d];
-  struct Item {
-    const int64_t* idx;
-    const uint16_t* val;
-    uint64_t ub;            // at most this many entries
-    const uint64_t* d_n;    // its count on the device (NULL: exactly ub)
-  };
-  std::vector<Item> items;
+  std::vector<CmpRun> items;
   for (int32_t d = 0; d < K; ++d) items.push_back({idx[d], val[d], counts[d], nullptr});
   if (K == 1) items.push_back({nullptr, nullptr, 0, nullptr});
   uint64_t* slots = (uint64_t*)(ws + L.counts);
   uint32_t slot = 0;
   uint64_t round = 0;
   while (items.size() > 1) {
-    const bool last = items.size() == 2;
+    const uint64_t groups = cmp_groups(items.size());
     char* region = ws + L.inter + round * (align_up(8 * total) + align_up(2 * total));
     int64_t* r_idx = (int64_t*)region;
     uint16_t* r_val = (uint16_t*)(region + align_up(8 * total));
     uint64_t r_off = 0;
-    std::vector<Item> next;
-    for (size_t p = 0; p + 1 < items.size(); p += 2) {
-      const Item& x = items[p];
-      const Item& y = items[p + 1];
+    std::vector<CmpRun> next;
+    for (uint64_t g = 0; g < groups; ++g) {
+      const size_t p0 = items.size() * g / groups, p1 = items.size() * (g + 1) / groups;
+      if (p1 - p0 == 1) {
+        next.push_back(items[p0]);
+        continue;
+      }
       ComposeArgs a;
       memset(&a, 0, sizeof(a));
-      a.a_idx = x.idx;
-      a.a_val = x.val;
-      a.na = x.ub;
-      a.d_na = x.d_n;
-      a.b_idx = y.idx;
-      a.b_val = y.val;
-      a.nb = y.ub;
-      a.d_nb = y.d_n;
+      uint64_t most = 0;
+      for (size_t p = p0; p < p1; ++p) {
+        a.run[a.runs++] = items[p];
+        most += items[p].n;
+      }
       a.err = err;
       uint64_t* cnt;
-      if (last) {
+      if (groups == 1) {
         a.out_idx = out_idx;
         a.out_val = out_val;
         a.capacity = capacity;
@@ -398,15 +622,14 @@ hipError_t launch_compose_chain(const int64_t* const* idx, const uint16_t* const
       } else {
         a.out_idx = r_idx + r_off;
         a.out_val = r_val + r_off;
-        a.capacity = x.ub + y.ub;
+        a.capacity = most;
         cnt = slots + slot++;
       }
-      hipError_t e = launch_compose2(a, ws + L.scratch, cnt, stream);
+      const hipError_t e = launch_compose_runs(a, ws + L.scratch, cnt, stream);
       if (e != hipSuccess) return e;
-      next.push_back({a.out_idx, a.out_val, x.ub + y.ub, cnt});
-      r_off += x.ub + y.ub;
+      next.push_back({a.out_idx, a.out_val, most, cnt});
+      r_off += most;
     }
-    if (items.size() % 2) next.push_back(items.back());
     items.swap(next);
     ++round;
   }

@@ -396,11 +396,13 @@ __global__ __launch_bounds__(kScanThreads) void group_scan_kernel(const uint64_t
   if (threadIdx.x == 0) *d_count = total;
 }
 
-// Up to 1024 groups (65536 tiles): the group sums and their scan in one
-// workgroup, one launch instead of two.  Wavefront w sums groups w, w + 16,
+// Up to 256 groups (16384 tiles): the group sums and their scan in one
+// workgroup, one launch instead of two (704 groups: 36 us against 14 for the
+// two launches; 200 groups: 5.4 against 9).  Wavefront w sums groups w, w + 16,
 // ... (4 of them per round, loads coalesced), into LDS; then every thread
 // scans one group.
-constexpr uint64_t kSmallScanGroups = kScanThreads;
+constexpr uint64_t kSmallScanGroups = 256;
+static_assert(kSmallScanGroups <= (uint64_t)kScanThreads, "a thread per group");
 
 template <typename CountT>
 __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(const CountT* counts,

@@ -1,0 +1,68 @@
+"""The one-round merge of up to eight runs against the oracle's composition:
+run lengths around the sample steps, runs of very different density (tiles
+that overfill and are taken in windows), ranges of values that pass the bits
+of the count pass and 32-bit offsets, and many equal indices."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2602_11456_amd as ad
+
+pytestmark = pytest.mark.gpu
+
+
+def check(idxs, seed):
+    rng = np.random.default_rng(seed)
+    host = [(np.asarray(i, dtype=np.int64), rng.integers(0, 1 << 16, len(i), dtype=np.uint16))
+            for i in idxs]
+    want_idx, want_val = oracle.compose(host)[:2]
+    dev = [(torch.from_numpy(i).cuda(), torch.from_numpy(v.view(np.int16)).cuda())
+           for i, v in host]
+    idx, val = ad.delta_compose(dev)
+    np.testing.assert_array_equal(idx.cpu().numpy(), want_idx)
+    np.testing.assert_array_equal(val.cpu().numpy().view(np.uint16), want_val)
+
+
+def draw(rng, lo, hi, n):
+    n = min(n, hi - lo)
+    return np.sort(rng.choice(hi - lo, n, replace=False)) + lo
+
+
+@pytest.mark.parametrize("runs", [2, 3, 4, 5, 7, 8, 9, 17])
+@pytest.mark.parametrize("length", [-1, 0, 1])
+def test_lengths_around_the_samples(runs, length):
+    step = 3520 // min(runs, 8)
+    rng = np.random.default_rng(100 * runs + length)
+    for mult in (1, 2, 5):
+        n = step * mult + length
+        check([draw(rng, 0, 20 * n, n) for _ in range(runs)], runs)
+
+
+@pytest.mark.parametrize("runs", [2, 3, 4, 6, 8])
+def test_uneven_runs(runs):
+    """One dense stretch per run at its own place, the rest thin: the runs'
+    samples bunch, and tiles hold up to twice what an even one does."""
+    rng = np.random.default_rng(runs)
+    idxs = []
+    for k in range(runs):
+        dense = draw(rng, 50_000 * k, 50_000 * k + 9_000, 8_000)
+        thin = draw(rng, 0, 1_000_000, 1_500)
+        idxs.append(np.unique(np.concatenate([dense, thin])))
+    check(idxs, 1)
+    check([draw(rng, 0, 40_000, 30_000)] + [draw(rng, 0, 4_000_000, 200)] * (runs - 1), 2)
+    check([np.arange(0, 60_000)] * runs, 3)                       # the same indices in each
+    check([np.arange(k, 80_000, runs) for k in range(runs)], 4)   # none in two
+
+
+@pytest.mark.parametrize("runs", [2, 4, 8])
+@pytest.mark.parametrize("scale", [50, 60, 1 << 20, 1 << 33])
+def test_spans(runs, scale):
+    """Tiles that span fewer and more values than the count pass has bits,
+    and more than 32-bit offsets reach; the least and greatest indices."""
+    rng = np.random.default_rng(runs + scale % 1000)
+    n = 4_000
+    idxs = [draw(rng, 0, 30 * n, n) * scale - (scale if k % 2 else 0) for k in range(runs)]
+    idxs[0] = np.concatenate([[np.iinfo(np.int64).min], idxs[0], [np.iinfo(np.int64).max]])
+    idxs[-1] = np.concatenate([idxs[-1], [np.iinfo(np.int64).max - 1, np.iinfo(np.int64).max]])
+    check(idxs, 5)
