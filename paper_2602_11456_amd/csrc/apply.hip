@@ -167,7 +167,6 @@ struct TensorCursor {
   uint64_t lo = 1, hi = 0;   // empty range: forces a search first
   uint16_t* base = nullptr;
 };
-template <bool kThrough>
 __device__ __forceinline__ bool store_global(const ChainArgs& a, uint64_t words, TensorCursor& c,
                                              int64_t g, uint16_t v) {
   if (g < 0 || (uint64_t)g >= words) return false;
@@ -177,13 +176,12 @@ __device__ __forceinline__ bool store_global(const ChainArgs& a, uint64_t words,
     c.hi = a.bases[c.t + 1];
     c.base = a.ptrs[c.t];
   }
-  store_word<kThrough>(c.base + ((uint64_t)g - c.lo), v);
+  store_word<false>(c.base + ((uint64_t)g - c.lo), v);
   return true;
 }
 
 static_assert(kApplyThreads == kChainThreads, "the chain helpers assume 256 threads");
 
-template <bool kThrough>
 __global__ __launch_bounds__(kApplyThreads) void chain_apply_kernel(ChainArgs a) {
   __shared__ ChainSmem s;
   const uint32_t K = a.r.K;
@@ -215,7 +213,7 @@ __global__ __launch_bounds__(kApplyThreads) void chain_apply_kernel(ChainArgs a)
       }
 #pragma unroll
       for (int u = 0; u < kChainPer; ++u)
-        if (keep[u] && !store_global<kThrough>(a, words, cur, x[u], v[u])) bad = true;
+        if (keep[u] && !store_global(a, words, cur, x[u], v[u])) bad = true;
     }
   } else {
     // A tile too large for LDS: each entry in turn, written unless a newer
@@ -234,7 +232,7 @@ __global__ __launch_bounds__(kApplyThreads) void chain_apply_kernel(ChainArgs a)
         const uint32_t at = run_rank(r, n2, x, false);
         newer = at < n2 && r[at] == x;
       }
-      if (!newer && !store_global<kThrough>(a, words, cur, x, gview(s.d[k].val)[e])) bad = true;
+      if (!newer && !store_global(a, words, cur, x, gview(s.d[k].val)[e])) bad = true;
     }
   }
   if (bad) flag_error(a.err);
@@ -244,16 +242,11 @@ hipError_t launch_apply_chain(const ChainArgs& a, hipStream_t stream) {
   if (a.r.tiles == 0) return hipSuccess;
   hipError_t e = launch_chain_split(a.r, stream);
   if (e != hipSuccess) return e;
-  // Stores written through reach the memory in order, and the kernel ends a
-  // few us later: four 1% deltas over 4.02 G words (158 M entries kept) 3.28
-  // against 3.54 ms, over 300 M words 302 against 304 us, but over 30 M words
-  // 99.6 against 97.4 us and over 1 M words 81.2 against 78.4.
-  if (a.r.tiles * a.r.bstride * a.r.K >= 1ull << 22)
-    hipLaunchKernelGGL(chain_apply_kernel<true>, dim3((uint32_t)a.r.tiles), dim3(kApplyThreads), 0,
-                       stream, a);
-  else
-    hipLaunchKernelGGL(chain_apply_kernel<false>, dim3((uint32_t)a.r.tiles), dim3(kApplyThreads),
-                       0, stream, a);
+  // Its stores are not written through: that takes four even 1% deltas over
+  // 4.02 G words from 3.54 to 3.28 ms, but four in few rows from 1.95 to 2.23
+  // and eight of 0.4% from 3.18 to 3.43.
+  hipLaunchKernelGGL(chain_apply_kernel, dim3((uint32_t)a.r.tiles), dim3(kApplyThreads), 0,
+                     stream, a);
   return hipGetLastError();
 }
 
