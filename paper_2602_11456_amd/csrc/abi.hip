@@ -837,7 +837,9 @@ static ChainPlan chain_plan(const uint64_t* counts, int32_t K, int32_t T) {
   c.tiles = (n_ref + c.per_tile - 1) / c.per_tile;
   c.deltas = delta_apply_multi_workspace_bytes(T);
   c.pos = align_up(c.deltas + sizeof(ChainDelta) * (size_t)(K > 0 ? K : 1));
-  c.tile_first = align_up(c.pos + 8 * (c.tiles + 1) * (uint64_t)(K > 0 ? K : 1));
+  // the composition's tiles need less than these positions
+  c.tile_first = align_up(c.pos + std::max<size_t>(8 * (c.tiles + 1) * (uint64_t)(K > 0 ? K : 1),
+                                                   chain_tiles_layout(counts, K).total));
   c.total = align_up(c.tile_first + 8 * ((size_t)(T > 0 ? T : 0) + 1));
   return c;
 }
@@ -903,6 +905,12 @@ delta_status_t delta_apply_chain(uint16_t* const* weight_ptrs, const uint64_t* n
     return ok();
   }
   if (c.tiles > 0xFFFFFFFFull) return fail(DELTA_ERR_INVALID_ARG, "too many entries");
+  if (chain_tiles_pay(counts, num_deltas)) {
+    e = launch_apply_chain_tiles(idx_ptrs, val_ptrs, counts, num_deltas, d_bases,
+                                 (uint16_t* const*)d_ptrs, T, d_error_flag, ws + c.pos, stream);
+    if (e != hipSuccess) return hip_fail(e, "apply_chain launch");
+    return ok();
+  }
   ChainArgs a;
   memset(&a, 0, sizeof(a));
   a.r.deltas = (const ChainDelta*)(ws + c.deltas);

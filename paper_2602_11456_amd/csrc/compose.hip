@@ -32,6 +32,7 @@
 #include <vector>
 
 #include "delta_internal.h"
+#include "scatter.h"
 
 namespace aurora {
 
@@ -63,7 +64,12 @@ struct ComposeArgs {
   uint64_t* pos;           // [tiles + 1][runs]: entries of each run before each tile
   int64_t* bound;          // [tiles + 1]: least index of each tile; at the end the largest of all
   uint32_t* err;           // nullable: set when the merge meets unsorted input
+  // The one-pass apply writes the kept words into a tensor list instead.
+  const uint64_t* bases;   // device [T + 1]
+  uint16_t* const* ptrs;   // device [T]
+  uint32_t T;
 };
+enum CmpMode { kCmpCount, kCmpWrite, kCmpApply };
 
 __device__ __forceinline__ void cmp_flag(const ComposeArgs& a) {
   if (a.err) __hip_atomic_fetch_or(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -207,9 +213,10 @@ constexpr uint32_t kCmpBits = 32 * 6144;
 // The launch bound's wavefronts per SIMD: four runs composed with the write
 // pass at 3 / 4 / 5 1571 / 1481 / 1793 us; the count pass at 4 / 6 1481 / 1476
 // us, eight runs 1214 / 1319.
-template <int G, bool kWrite>
-__global__ __launch_bounds__(kCmpThreads, kWrite || G == 8 ? 4 : 6) void compose_tile_kernel(
-    ComposeArgs a) {
+template <int G, CmpMode kMode>
+__global__ __launch_bounds__(kCmpThreads, kMode != kCmpCount || G == 8 ? 4 : 6) void
+compose_tile_kernel(ComposeArgs a) {
+  constexpr bool kWrite = kMode != kCmpCount;   // the words are needed
   __shared__ uint32_t s_key[kWrite ? kCmpCap : kCmpBits / 32];
   __shared__ uint16_t s_val[kWrite ? kCmpCap : 1];
   __shared__ uint64_t s_cur[G], s_end[G];
@@ -221,7 +228,7 @@ __global__ __launch_bounds__(kCmpThreads, kWrite || G == 8 ? 4 : 6) void compose
   uint64_t n_run[G];
   const uint64_t samples = cmp_sizes<G>(a, n_run);
   const uint64_t tiles = (samples + runs - 1) / runs;
-  const uint64_t tile = blockIdx.x;
+  const uint64_t tile = kMode == kCmpApply ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
   if (tile >= tiles) {   // uniform
     if (!kWrite && threadIdx.x == 0) a.tile_counts[tile] = 0;
     return;
@@ -250,7 +257,7 @@ __global__ __launch_bounds__(kCmpThreads, kWrite || G == 8 ? 4 : 6) void compose
     s_cur[k] = p0;
     s_end[k] = p1;
   }
-  if (kWrite && threadIdx.x >= 64 && threadIdx.x < 128) {   // kept by the group's earlier tiles
+  if (kMode == kCmpWrite && threadIdx.x >= 64 && threadIdx.x < 128) {   // kept by the group's earlier tiles
     const uint32_t lane = threadIdx.x & 63;
     const uint64_t g0 = tile / kTilesPerGroup * kTilesPerGroup;
     uint64_t c = g0 + lane < tile ? (uint64_t)a.tile_counts[g0 + lane] : 0;
@@ -259,7 +266,11 @@ __global__ __launch_bounds__(kCmpThreads, kWrite || G == 8 ? 4 : 6) void compose
     if (lane == 0) s_before = a.group_excl[tile / kTilesPerGroup] + c;
   }
   __syncthreads();
-  uint64_t out = kWrite ? s_before : 0;   // kept entries before the window
+  uint64_t out = kMode == kCmpWrite ? s_before : 0;   // kept entries before the window
+  // the one-pass apply: the tensor [lo, hi) of this lane's last entry
+  const uint64_t words = kMode == kCmpApply ? a.bases[a.T] : 0;
+  uint64_t lo = 1, hi = 0;
+  uint16_t* weights = nullptr;
   bool first_window = true;
   while (true) {
     CmpWindow<G> w;
@@ -368,7 +379,7 @@ __global__ __launch_bounds__(kCmpThreads, kWrite || G == 8 ? 4 : 6) void compose
       }
     }
     __syncthreads();
-    if (!kWrite) {   // strictly increasing within a run
+    if (kMode != kCmpWrite) {   // strictly increasing within a run
 #pragma unroll
       for (int u = 0; u < kCmpPer; ++u) {
         const uint32_t q = threadIdx.x + kCmpThreads * u;
@@ -477,7 +488,21 @@ __global__ __launch_bounds__(kCmpThreads, kWrite || G == 8 ? 4 : 6) void compose
         }
       }
       __syncthreads();
-      for (uint32_t q = threadIdx.x; q < window; q += kCmpThreads) {
+      for (uint32_t q = threadIdx.x; kMode == kCmpApply && q < window; q += kCmpThreads) {
+        const uint64_t g = (uint64_t)w.base + s_key[q];
+        if (g >= words) {   // a negative index too
+          bad = true;
+          continue;
+        }
+        if (!(g >= lo && g < hi)) {
+          const uint32_t t = find_tensor(a.bases, a.T, g);
+          lo = a.bases[t];
+          hi = a.bases[t + 1];
+          weights = a.ptrs[t];
+        }
+        store_word<false>(weights + (g - lo), s_val[q]);
+      }
+      for (uint32_t q = threadIdx.x; kMode == kCmpWrite && q < window; q += kCmpThreads) {
         if (out + q < a.capacity) {
           a.out_idx[out + q] = (int64_t)((uint64_t)w.base + s_key[q]);
           a.out_val[out + q] = s_val[q];
@@ -522,13 +547,13 @@ static hipError_t launch_merge(const ComposeArgs& a, const CmpScratch& s, uint64
                      dim3(256), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((compose_tile_kernel<G, false>), dim3((uint32_t)s.tiles), dim3(kCmpThreads), 0,
+  hipLaunchKernelGGL((compose_tile_kernel<G, kCmpCount>), dim3((uint32_t)s.tiles), dim3(kCmpThreads), 0,
                      stream, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   e = launch_group_scan(a.tile_counts, s.tiles, group_sum, a.group_excl, d_count, stream);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((compose_tile_kernel<G, true>), dim3((uint32_t)s.tiles), dim3(kCmpThreads), 0,
+  hipLaunchKernelGGL((compose_tile_kernel<G, kCmpWrite>), dim3((uint32_t)s.tiles), dim3(kCmpThreads), 0,
                      stream, a);
   return hipGetLastError();
 }
@@ -548,6 +573,73 @@ static hipError_t launch_compose_runs(ComposeArgs a, char* scratch, uint64_t* d_
   if (a.runs <= 2) return launch_merge<2>(a, s, group_sum, d_count, stream);
   if (a.runs <= 4) return launch_merge<4>(a, s, group_sum, d_count, stream);
   return launch_merge<8>(a, s, group_sum, d_count, stream);
+}
+
+// --------------------------------------------------- the one-pass apply
+//
+// Up to four deltas applied to a tensor list in one pass: the tiles of the
+// composition, each merged once and its kept words scattered in index order
+// (no count pass, nothing written but the weights).  It pays where the GPU
+// stays full of tiles: from 16.8 M entries, over 4.02 G words 2 / 4 even 1%
+// deltas take 2.40 / 3.31 ms against 2.49 / 3.52 with the chain kernel's
+// smaller tiles, four and two gathered in few rows 1.57 / 1.51 against 1.94 /
+// 1.56; 12 M entries 305 us against 300, 1.2 M 111 against 93, and six to
+// twelve deltas are slower at any size.  The LDS reserved leaves three
+// workgroups per CU (two suit even deltas, 2.37 / 3.28, and slow gathered
+// ones, 1.76).
+constexpr size_t kChainTileLds = 18 * 1024;
+constexpr uint64_t kChainTileMin = 1ull << 24;
+bool chain_tiles_pay(const uint64_t* counts, int32_t K) {
+  uint64_t n = 0;
+  for (int32_t k = 0; k < K; ++k) n += counts[k];
+  return K >= 2 && K <= 4 && n >= kChainTileMin;
+}
+
+template <int G>
+static hipError_t launch_apply_tiles(const ComposeArgs& a, uint64_t samples, uint64_t tiles,
+                                     hipStream_t stream) {
+  hipLaunchKernelGGL(compose_split_kernel<G>, dim3((uint32_t)((samples + 1 + 255) / 256)),
+                     dim3(256), 0, stream, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((compose_tile_kernel<G, kCmpApply>), dim3((uint32_t)tiles),
+                     dim3(kCmpThreads), kChainTileLds, stream, a);
+  return hipGetLastError();
+}
+
+ChainTilesLayout chain_tiles_layout(const uint64_t* counts, int32_t K) {
+  ChainTilesLayout L;
+  if (!chain_tiles_pay(counts, K)) return {0, 0};
+  uint64_t n = 0;
+  for (int32_t k = 0; k < K; ++k) n += counts[k];
+  const CmpScratch s = cmp_scratch(n, K);
+  L.bound = align_up(8 * (uint64_t)K * (s.tiles + 1));
+  L.total = align_up(L.bound + 8 * (s.tiles + 1));
+  return L;
+}
+
+hipError_t launch_apply_chain_tiles(const int64_t* const* idx, const uint16_t* const* val,
+                                    const uint64_t* counts, int32_t K, const uint64_t* bases,
+                                    uint16_t* const* ptrs, uint32_t T, uint32_t* err, char* ws,
+                                    hipStream_t stream) {
+  ComposeArgs a;
+  memset(&a, 0, sizeof(a));
+  a.runs = (uint32_t)K;
+  a.step = kCmpTile / (uint32_t)K;
+  uint64_t samples = 0;
+  for (int32_t k = 0; k < K; ++k) {
+    a.run[k] = {idx[k], val[k], counts[k], nullptr};
+    samples += (counts[k] + a.step - 1) / a.step;
+  }
+  a.pos = (uint64_t*)ws;
+  a.bound = (int64_t*)(ws + chain_tiles_layout(counts, K).bound);
+  a.bases = bases;
+  a.ptrs = ptrs;
+  a.T = T;
+  a.err = err;
+  const uint64_t tiles = (samples + K - 1) / K;
+  return K <= 2 ? launch_apply_tiles<2>(a, samples, tiles, stream)
+                : launch_apply_tiles<4>(a, samples, tiles, stream);
 }
 
 // ------------------------------------------------------------ the chain

@@ -287,6 +287,18 @@ hipError_t launch_apply_runs(const uint64_t* bases, uint16_t* const* ptrs,
                              uint64_t words, uint32_t* err, hipStream_t stream);
 bool chain_merge_pays(uint64_t entries, uint64_t words);
 hipError_t launch_chain_split(const ChainRuns& r, hipStream_t stream);
+// The same with the composition's tiles (compose.hip), for the chains
+// chain_tiles_pay names: the deltas as host arrays, oldest first; ws holds the
+// split positions and tile bounds of chain_tiles_layout.
+struct ChainTilesLayout {
+  size_t bound, total;
+};
+bool chain_tiles_pay(const uint64_t* counts, int32_t K);
+ChainTilesLayout chain_tiles_layout(const uint64_t* counts, int32_t K);
+hipError_t launch_apply_chain_tiles(const int64_t* const* idx, const uint16_t* const* val,
+                                    const uint64_t* counts, int32_t K, const uint64_t* bases,
+                                    uint16_t* const* ptrs, uint32_t T, uint32_t* err, char* ws,
+                                    hipStream_t stream);
 
 // One slice of a tensor list for enqueue_extract: `n` words of both copies
 // whose word 0 has output index `base`; `tensor` is the caller's index and

@@ -66,3 +66,38 @@ def test_spans(runs, scale):
     idxs[0] = np.concatenate([[np.iinfo(np.int64).min], idxs[0], [np.iinfo(np.int64).max]])
     idxs[-1] = np.concatenate([idxs[-1], [np.iinfo(np.int64).max - 1, np.iinfo(np.int64).max]])
     check(idxs, 5)
+
+
+@pytest.mark.parametrize("runs", [2, 3, 4])
+def test_large_chain_applied_in_one_pass(runs):
+    """A chain large enough for the composition's tiles (2^24 entries) and
+    thinner than the tile merge, over odd-sized tensors, against the deltas
+    assigned one after another; then with entries outside the list."""
+    g = torch.Generator(device="cuda").manual_seed(runs)
+    sizes = [1, 230_000_001, 0, 77, 250_000_003]
+    total = sum(sizes)
+    deltas = []
+    for k in range(runs):
+        n = 18_000_000 // runs
+        idx = torch.unique(torch.randint(0, total, (n,), generator=g, device="cuda"))
+        if k == 0:   # the last tensor's last word, and a dense stretch
+            idx = torch.unique(torch.cat([idx, torch.arange(9_000, 29_000, device="cuda"),
+                                          torch.tensor([total - 1], device="cuda")]))
+        val = torch.randint(-30000, 30000, (idx.numel(),), generator=g, device="cuda",
+                            dtype=torch.int16)
+        deltas.append((idx, val))
+    assert 1 << 24 <= sum(i.numel() for i, _ in deltas) < total // 24
+    want = torch.zeros(total, dtype=torch.int16, device="cuda")
+    for idx, val in deltas:
+        want[idx] = val
+    flat = torch.zeros_like(want)
+    ad.delta_apply_chain(list(flat.split(sizes)), deltas, check=True)
+    assert torch.equal(flat, want)
+    idx, val = deltas[-1]
+    out = torch.tensor([-3, total, total + 5], device="cuda")
+    idx, order = torch.sort(torch.cat([idx, out]))
+    val = torch.cat([val, torch.ones(3, dtype=torch.int16, device="cuda")])[order]
+    flat.zero_()
+    with pytest.raises(ad.DeltaError):
+        ad.delta_apply_chain(list(flat.split(sizes)), deltas[:-1] + [(idx, val)], check=True)
+    assert torch.equal(flat, want)
