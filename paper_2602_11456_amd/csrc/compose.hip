@@ -664,9 +664,10 @@ ChainLayout chain_layout(const uint64_t* counts, int32_t K) {
   for (uint64_t r = 2; r <= (uint64_t)kCmpRuns; ++r)
     if (r == 2 || (int64_t)r <= K) scratch = std::max(scratch, cmp_scratch(total, r).total);
   L.counts = align_up(scratch);
-  L.inter = align_up(L.counts + 8 * (uint64_t)(K > 0 ? K : 1));
-  const uint64_t inter_rounds = rounds > 1 ? rounds - 1 : 0;
-  L.total = align_up(L.inter + inter_rounds * (align_up(8 * total) + align_up(2 * total)));
+  const size_t counts_end = L.counts + 8 * (uint64_t)(K > 0 ? K : 1);
+  L.inter = align_up(counts_end);
+  L.total = counts_end;   // nothing behind the counts in a chain of one round
+  if (rounds > 1) L.total = L.inter + (rounds - 1) * (align_up(8 * total) + align_up(2 * total));
   return L;
 }
 
