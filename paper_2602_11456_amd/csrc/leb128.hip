@@ -199,6 +199,20 @@ __device__ __forceinline__ void enc_load(const EncArgs& a, uint64_t kw, uint64_t
   L.last = (first > 0 && first < t1) ? a.idx[first - 1] : 0;
 }
 
+// The lane's neighbour below's x; lane 0 takes `first` (wave shift right by
+// one, on the vector unit: a shuffle would pass through LDS).
+__device__ __forceinline__ int64_t lane_before(int64_t x, int64_t first) {
+  const int lo = __builtin_amdgcn_update_dpp((int)first, (int)x, 0x138, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp((int)(first >> 32), (int)(x >> 32), 0x138, 0xF, 0xF,
+                                             false);
+  return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+__device__ __forceinline__ int64_t last_lane(int64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, 63);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)((uint64_t)x >> 32), 63);
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 // Gaps of the loaded entries: idx - base for an entry that opens its
 // segment, else idx - previous idx (the previous index comes from the
 // neighbouring lane).  Sets bit it of `starts` for an entry that opens a
@@ -208,7 +222,6 @@ __device__ __forceinline__ void enc_load(const EncArgs& a, uint64_t kw, uint64_t
 __device__ __forceinline__ uint32_t enc_gaps(const EncArgs& a, const TileSegs& c,
                                              const uint64_t* s_lo, uint64_t kw, uint64_t t1,
                                              EncLoad& L, uint32_t& starts, bool& bad) {
-  const uint32_t lane = lane_id();
   int64_t last = L.last;
   uint32_t bytes = 0;
   starts = 0;
@@ -216,9 +229,8 @@ __device__ __forceinline__ uint32_t enc_gaps(const EncArgs& a, const TileSegs& c
   for (int it = 0; it < kEncSteps; ++it) {
     const uint64_t k = kw + 64 * it;
     const int64_t cur = L.cur[it];
-    int64_t prev = __shfl_up(cur, 1);
-    if (lane == 0) prev = last;
-    last = __shfl(cur, 63);
+    const int64_t prev = lane_before(cur, last);
+    last = last_lane(cur);
     uint64_t g = 0;
     if (k < t1) {
       bool start;
@@ -240,9 +252,15 @@ __device__ __forceinline__ uint32_t enc_gaps(const EncArgs& a, const TileSegs& c
   return bytes;
 }
 
-// Position of every entry's code inside the tile (wavefront scans of the
-// lengths, starting at `pos`, this wavefront's offset in the tile); calls
-// f(it, k, len, p, gap) for each of the lane's entries inside the tile.
+// Position of every entry's code inside the tile (from `pos`, this
+// wavefront's offset in the tile); calls f(it, k, len, p, gap, two) for each
+// of the lane's entries inside the tile, `two` if no number of the
+// wavefront's step takes over two bytes.  The lengths before a lane are
+// counted from ballots of their bits: a scan by shuffles takes seven trips
+// through LDS a step, and a wavefront did little else.  Packing the artifact
+// of a 1% delta over 4.02 G words (40 M entries) takes 388 us, with shuffles
+// here and for the gaps, and single bytes read where enc_copy's pieces are
+// put together, 424.
 template <typename F>
 __device__ __forceinline__ void enc_walk(uint64_t kw, uint64_t t1, const int64_t (&gap)[kEncSteps],
                                          uint32_t pos, F f) {
@@ -251,9 +269,17 @@ __device__ __forceinline__ void enc_walk(uint64_t kw, uint64_t t1, const int64_t
     const uint64_t k = kw + 64 * it;
     const uint64_t g = (uint64_t)gap[it];
     const uint32_t len = k < t1 ? leb_len(g) : 0;
-    const uint32_t incl = wave_incl_scan(len);
-    if (len) f(it, k, len, pos + incl - len, g);
-    pos += __shfl(incl, 63);
+    const uint64_t b0 = __ballot(len & 1), b1 = __ballot(len & 2);
+    uint32_t before = lanes_below(b0) + 2 * lanes_below(b1);
+    uint32_t all = __builtin_popcountll(b0) + 2 * __builtin_popcountll(b1);
+    const bool two = __ballot(len > 2) == 0;
+    if (!two) {   // uniform
+      const uint64_t b2 = __ballot(len & 4), b3 = __ballot(len & 8);
+      before += 4 * lanes_below(b2) + 8 * lanes_below(b3);
+      all += 4 * __builtin_popcountll(b2) + 8 * __builtin_popcountll(b3);
+    }
+    if (len) f(it, k, len, pos + before, g, two);
+    pos += all;
   }
 }
 
@@ -330,7 +356,8 @@ __global__ __launch_bounds__(kLebThreads) void enc_stage_kernel(EncArgs a) {
     }
     const bool staged = total <= kEncSlot;
     const bool segs_out = a.seg_byte_offsets && a.segs.num;
-    enc_walk(kw, t1, L.cur, pos, [&](int it, uint64_t k, uint32_t len, uint32_t p, uint64_t v) {
+    enc_walk(kw, t1, L.cur, pos, [&](int it, uint64_t k, uint32_t len, uint32_t p, uint64_t v,
+                                     bool two) {
       if (segs_out && ((starts >> it) & 1u)) {
         // this entry opens its segment and every empty one just before it:
         // their tile-local offset (made absolute by enc_seg_fix)
@@ -338,7 +365,13 @@ __global__ __launch_bounds__(kLebThreads) void enc_stage_kernel(EncArgs a) {
         const uint32_t sg = tile_seg(a.segs, c, s_lo, k, st);
         for (int64_t s = sg; s >= 0 && a.segs.offs[s] == k; --s) a.seg_byte_offsets[s] = p;
       }
-      if (staged) enc_bytes(v, len, [&](uint32_t m, uint8_t b) { s_out[p + m] = b; });
+      if (staged && two) {
+        const uint32_t x = (uint32_t)v;
+        s_out[p] = (uint8_t)((x & 0x7F) | (len == 2 ? 0x80u : 0u));
+        if (len == 2) s_out[p + 1] = (uint8_t)(x >> 7);
+      } else if (staged) {
+        enc_bytes(v, len, [&](uint32_t m, uint8_t b) { s_out[p + m] = b; });
+      }
     });
     __syncthreads();
     if (staged) {
@@ -362,29 +395,35 @@ __global__ __launch_bounds__(64) void enc_group_sum_kernel(EncArgs a, uint64_t* 
   if (lane_id() == 0) group_sum[blockIdx.x] = v;
 }
 
-// Stores bytes [0, n) of s_out at out + pos (4-byte stores where the
-// destination is aligned).
+// Stores bytes [0, n) of s_out (16-byte aligned, readable for 16 bytes past
+// n) at out + pos, in 16-byte pieces of the destination; each is put together
+// from five aligned words.
 __device__ __forceinline__ void enc_flush(const uint8_t* s_out, uint64_t n, uint8_t* out,
                                           uint64_t pos) {
   uint8_t* dst = out + pos;
-  const uint64_t head = (4 - ((uintptr_t)dst & 3u)) & 3u;
+  const uint64_t head = (16 - ((uintptr_t)dst & 15u)) & 15u;
   const uint64_t h = head < n ? head : n;
-  const uint64_t words = (n - h) / 4;
-  for (uint64_t i = threadIdx.x; i < h; i += kLebThreads) dst[i] = s_out[i];
-  uint32_t* dw = (uint32_t*)(dst + h);
-  for (uint64_t w = threadIdx.x; w < words; w += kLebThreads) {
-    const uint64_t j = h + 4 * w;
-    dw[w] = (uint32_t)s_out[j] | ((uint32_t)s_out[j + 1] << 8) | ((uint32_t)s_out[j + 2] << 16) |
-            ((uint32_t)s_out[j + 3] << 24);
+  const uint64_t pieces = (n - h) / 16;
+  if (threadIdx.x < h) dst[threadIdx.x] = s_out[threadIdx.x];
+  const uint32_t* src = (const uint32_t*)s_out + h / 4;
+  const uint32_t shift = (uint32_t)h & 3;   // alignbyte: bytes to drop from the low word
+  enc_u32x4* d4 = (enc_u32x4*)(dst + h);
+  for (uint64_t i = threadIdx.x; i < pieces; i += kLebThreads) {
+    const uint32_t* w = src + 4 * i;
+    enc_u32x4 x;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = __builtin_amdgcn_alignbyte(w[j + 1], w[j], shift);
+    d4[i] = x;
   }
-  for (uint64_t i = h + 4 * words + threadIdx.x; i < n; i += kLebThreads) dst[i] = s_out[i];
+  const uint64_t t = h + 16 * pieces + threadIdx.x;
+  if (t < n) dst[t] = s_out[t];   // fewer than 16
 }
 
 __global__ __launch_bounds__(kLebThreads) void enc_copy_kernel(EncArgs a) {
   __shared__ uint64_t s_lo[kSegLds];
   __shared__ uint32_t s_wave[kLebWaves];
   __shared__ uint64_t s_before;
-  __shared__ __align__(16) uint8_t s_out[kEncSlot];
+  __shared__ __align__(16) uint8_t s_out[kEncSlot + 16];
   const uint64_t count = enc_count_of(a);
   const uint64_t tiles = (count + kEncTile - 1) / kEncTile;
   const uint32_t lane = lane_id(), wave = wave_id();
@@ -427,7 +466,7 @@ __global__ __launch_bounds__(kLebThreads) void enc_copy_kernel(EncArgs a) {
       uint32_t pos = 0;
 #pragma unroll
       for (int w = 0; w < kLebWaves; ++w) pos += (uint32_t)w < wave ? s_wave[w] : 0u;
-      enc_walk(kw, t1, L.cur, pos, [&](int, uint64_t, uint32_t len, uint32_t p, uint64_t v) {
+      enc_walk(kw, t1, L.cur, pos, [&](int, uint64_t, uint32_t len, uint32_t p, uint64_t v, bool) {
         enc_bytes(v, len, [&](uint32_t m, uint8_t b) {
           if (tile_pos + p + m < a.capacity) a.out[tile_pos + p + m] = b;
         });
