@@ -1172,6 +1172,8 @@ delta_status_t delta_artifact_seal(void* d_artifact, size_t artifact_bytes,
 size_t delta_artifact_verify_workspace_bytes(const delta_artifact_header_t* header) {
   ArtifactLayout L;
   if (!layout_of(header, &L)) return 0;
+  // one hash per segment: required of the caller as ever, though the hashes
+  // are compared where they are formed
   return align_up(8 * (L.num_segments ? L.num_segments : 1));
 }
 
@@ -1194,8 +1196,8 @@ delta_status_t delta_artifact_verify(const void* d_artifact, size_t artifact_byt
       check_workspace(workspace, workspace_bytes, delta_artifact_verify_workspace_bytes(header));
   if (st != DELTA_OK) return st;
   hipError_t e = launch_artifact_verify((const uint8_t*)d_artifact, L, header->seg_bytes,
-                                        header->version, (uint64_t*)workspace, d_bad_segments,
-                                        d_first_bad, d_header_bad, stream);
+                                        header->version, d_bad_segments, d_first_bad,
+                                        d_header_bad, stream);
   if (e != hipSuccess) return hip_fail(e, "verify launch");
   return ok();
 }
@@ -1235,21 +1237,19 @@ PackLayout pack_layout(uint64_t count, int32_t T, bool leb) {
   return L;
 }
 
-// Workspace of delta_artifact_activate: the verify results and fresh
-// segment hashes, the segment offsets [T + 1], the error flag, then the
-// apply's own workspace.
+// Workspace of delta_artifact_activate: the verify results, the error flag,
+// the segment offsets [T + 1], then the apply's own workspace.
 struct ActivateLayout {
-  size_t bad, first_bad, header_bad, err, offs, fresh, apply, total;
+  size_t bad, first_bad, header_bad, err, offs, apply, total;
 };
-ActivateLayout activate_layout(const ArtifactLayout& A, const delta_artifact_header_t& h) {
+ActivateLayout activate_layout(const delta_artifact_header_t& h) {
   ActivateLayout L;
   L.bad = 0;
   L.first_bad = 8;
   L.header_bad = 16;
   L.err = 24;
   L.offs = align_up(32);
-  L.fresh = align_up(L.offs + 8 * (h.num_tensors + 1));
-  L.apply = align_up(L.fresh + 8 * (A.num_segments ? A.num_segments : 1));
+  L.apply = align_up(L.offs + 8 * (h.num_tensors + 1));
   const size_t apply_ws = h.index_coding == DELTA_CODING_LEB128
                               ? delta_apply_leb128_workspace_bytes(h.idx_bytes, (int32_t)h.num_tensors)
                               : delta_apply_multi_workspace_bytes((int32_t)h.num_tensors);
@@ -1388,7 +1388,7 @@ delta_status_t delta_artifact_pack(const int64_t* idx, const uint16_t* val, uint
 size_t delta_artifact_activate_workspace_bytes(const delta_artifact_header_t* header) {
   ArtifactLayout A;
   if (!layout_of(header, &A) || header->index_coding > DELTA_CODING_LEB128) return 0;
-  return activate_layout(A, *header).total;
+  return activate_layout(*header).total;
 }
 
 delta_status_t delta_artifact_activate(const void* d_artifact, size_t artifact_bytes,
@@ -1419,15 +1419,14 @@ delta_status_t delta_artifact_activate(const void* d_artifact, size_t artifact_b
     return fail(DELTA_ERR_INVALID_ARG, "the artifact is for %llu tensors of %llu words, got %d of %llu",
                 (unsigned long long)header->num_tensors, (unsigned long long)header->total_words,
                 num_tensors, (unsigned long long)bases[num_tensors]);
-  const ActivateLayout W = activate_layout(A, *header);
+  const ActivateLayout W = activate_layout(*header);
   st = check_workspace(workspace, workspace_bytes, W.total);
   if (st != DELTA_OK) return st;
   char* ws = (char*)workspace;
   const uint8_t* art = (const uint8_t*)d_artifact;
   // verify every segment hash and the artifact hash before touching the weights
   hipError_t e = launch_artifact_verify(art, A, header->seg_bytes, header->version,
-                                        (uint64_t*)(ws + W.fresh), (uint64_t*)(ws + W.bad),
-                                        (uint64_t*)(ws + W.first_bad),
+                                        (uint64_t*)(ws + W.bad), (uint64_t*)(ws + W.first_bad),
                                         (uint32_t*)(ws + W.header_bad), stream);
   if (e != hipSuccess) return hip_fail(e, "verify launch");
   uint64_t res[3];

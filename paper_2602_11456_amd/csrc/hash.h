@@ -32,8 +32,7 @@ hipError_t launch_artifact_table(uint8_t* art, const ArtifactLayout& L, const ui
 hipError_t launch_artifact_seal(uint8_t* art, const ArtifactLayout& L,
                                 const delta_artifact_header_t& h, hipStream_t stream);
 hipError_t launch_artifact_verify(const uint8_t* art, const ArtifactLayout& L, uint64_t seg_bytes,
-                                  uint64_t seed, uint64_t* fresh, uint64_t* d_bad,
-                                  uint64_t* d_first_bad, uint32_t* d_header_bad,
-                                  hipStream_t stream);
+                                  uint64_t seed, uint64_t* d_bad, uint64_t* d_first_bad,
+                                  uint32_t* d_header_bad, hipStream_t stream);
 
 }  // namespace aurora
